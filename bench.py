@@ -88,8 +88,15 @@ def jacobi_flops(M: int, sweeps, rotations, rank, Ns: int = 0, sub: bool = False
     return total
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "jacobi_persistent_60ch_257bin_hbm_traffic.json")
-JACOBI_SRC = os.path.join(ROOT, "paper_2504_03373_amd", "csrc", "jacobi.hip")
+def subspace_flops(M: int, applications: float = 3.0, block: int = 8) -> float:
+    """Algorithmic real flops of one bin's subspace iteration: the start block (A Omega) and
+    `applications` of A A^H (two products each) on `block` complex vectors, 8 M^2 per vector and
+    product; the 60-channel workload's bins take 2 to 4 applications (3 counted)."""
+    return (1.0 + 2.0 * applications) * block * 8.0 * M * M
+
+
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "subspace_batch_60ch_257bin_hbm_traffic.json")
+TRAFFIC_SRC = os.path.join(ROOT, "paper_2504_03373_amd", "csrc", "subspace.hip")
 
 
 def _sha256(path: str) -> str:
@@ -99,14 +106,14 @@ def _sha256(path: str) -> str:
 
 
 def traffic_bytes(batch: int):
-    """HBM bytes per Jacobi launch from the committed counter summary, or None when it is absent,
+    """HBM bytes per subspace-iteration launch from the committed counter summary, or None when it is absent,
     was taken at another batch size, or the kernel source has changed since."""
     try:
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
     except (OSError, ValueError):
         return None
-    if t.get("source_sha256") != _sha256(JACOBI_SRC) or t.get("blocks_per_launch") != batch:
+    if t.get("source_sha256") != _sha256(TRAFFIC_SRC) or t.get("blocks_per_launch") != batch:
         return None
     return t.get("bytes_per_launch")
 
@@ -127,25 +134,24 @@ def _pmc_rows(d: str, counter: str):
 
 
 def pmc_summarize(fetch_dir: str, write_dir: str, calib_mb: int, batch: int) -> int:
-    """FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of jacobi_persistent, each scaled by what the
+    """FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of subspace_batch, each scaled by what the
     same counter reads for the calibration kernel (calib_mb MiB read and written once)."""
     import numpy as np
     if calib_mb <= 0:
         raise SystemExit("--calib-copy-mb is needed to scale the counters")
     calib = calib_mb * (1 << 20)
-    out = {"kernel": "jacobi_persistent", "blocks_per_launch": batch,
-           "source_sha256": _sha256(JACOBI_SRC), "calibration_bytes": calib}
+    out = {"kernel": "subspace_batch", "blocks_per_launch": batch,
+           "source_sha256": _sha256(TRAFFIC_SRC), "calibration_bytes": calib}
     total = 0.0
     for name, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = _pmc_rows(d, name)
         cal = [v for k, v in rows if "neg" in k.lower()]
-        # the variant the timed steps ran: the most frequent one (the autotuner also launches the
-        # others a few times)
-        names = [k for k, _ in rows if "jacobi_persistent" in k]
+        # the class the timed steps ran: the most frequent one
+        names = [k for k, _ in rows if "subspace_batch" in k]
         top = max(set(names), key=names.count) if names else None
         jac = [v for k, v in rows if k == top]
         if not cal or not jac:
-            raise SystemExit(f"{name}: calibration or Jacobi dispatches missing in {d}")
+            raise SystemExit(f"{name}: calibration or subspace_batch dispatches missing in {d}")
         scale = calib / (max(cal) * 1024.0)
         per_launch = float(np.median(jac)) * 1024.0 * scale
         out[name.lower()] = {"kib_per_dispatch_median": float(np.median(jac)),
@@ -680,6 +686,9 @@ def main() -> int:
         sH = 8 if name == "fp32" else 4
         w_corr = B * (8.0 * F * T * M + 8.0 * F * M * M)
         w_white = B * 8.0 * F * M ** 3
+        # M > 16 through the signal subspace: one kernel forms A = K^{-1} R and iterates on it
+        iterated = sig and M > 16
+        w_iter = w_white + B * F * subspace_flops(M)
         # projection: |E_n^H h|^2 (M - Ns noise vectors, MFMA at the table's precision), or
         # through the signal subspace |E_s^H h|^2 (Ns vectors, FP64 MFMA)
         w_steer = B * 8.0 * F * D * M * (Ns if sig else M - Ns)
@@ -687,11 +696,12 @@ def main() -> int:
         rl = {
             "corr": {"bound": "hbm", "unit": "GB/s", "bytes_per_launch": w_corr,
                      "achieved": w_corr / ms("corr") / 1e9, "peak": PEAK_HBM_GBS},
-            "whiten": {"bound": "mfma", "mfma_dtype": "f64", "unit": "TFLOP/s",
-                       "flops_per_launch": w_white,
-                       "achieved": w_white / ms("whiten") / 1e12, "peak": PEAK_FP64_TFLOPS},
-            "jacobi": {"bound": "alu", "unit": "TFLOP/s", "flops_per_launch": jflops,
-                       "achieved": jflops / ms("jacobi") / 1e12, "peak": PEAK_FP32_VECTOR_TFLOPS},
+            "jacobi": {"bound": "mfma", "mfma_dtype": "f64", "unit": "TFLOP/s",
+                       "form": "whitening and subspace iteration", "flops_per_launch": w_iter,
+                       "achieved": w_iter / ms("jacobi") / 1e12, "peak": PEAK_FP64_TFLOPS}
+            if iterated else
+            {"bound": "alu", "unit": "TFLOP/s", "flops_per_launch": jflops,
+             "achieved": jflops / ms("jacobi") / 1e12, "peak": PEAK_FP32_VECTOR_TFLOPS},
             "steer": {"bound": "mfma", "mfma_dtype": "f64" if sig else name, "unit": "TFLOP/s",
                       "flops_per_launch": w_steer,
                       "achieved": w_steer / ms("steer") / 1e12,
@@ -701,12 +711,16 @@ def main() -> int:
             "binsum": {"bound": "hbm", "unit": "GB/s", "bytes_per_launch": w_bins,
                        "achieved": w_bins / ms("binsum") / 1e9, "peak": PEAK_HBM_GBS},
         }
+        if "whiten" in avg:
+            rl["whiten"] = {"bound": "mfma", "mfma_dtype": "f64", "unit": "TFLOP/s",
+                            "flops_per_launch": w_white,
+                            "achieved": w_white / ms("whiten") / 1e12, "peak": PEAK_FP64_TFLOPS}
         for v in rl.values():
             v["frac"] = round(v["achieved"] / v["peak"], 4)
             v["achieved"] = round(v["achieved"], 3)
         out = {"value": args.steps * B / elapsed, "elapsed": elapsed, "graph_value": graph_value,
                "per_block": per_block, "lat": lat, "kt": kt, "avg": avg, "rl": rl,
-               "jflops": jflops, "conv": conv_all, "status_ok": status_ok}
+               "jflops": rl["jacobi"]["flops_per_launch"], "iterated": iterated, "conv": conv_all, "status_ok": status_ok}
         if with_h2d:
             # X of every block from pinned host memory: (a) copy then compute on one stream;
             # (b) double-buffered, the copy of step k+1 on a side stream under step k
@@ -761,11 +775,14 @@ def main() -> int:
     f32 = main_r if args.prec == "fp32" else sec.get("fp32")
 
     avg = main_r["avg"]
-    roofline = {"kernel": "jacobi_persistent", **{k: main_r["rl"]["jacobi"][k] for k in
+    iterated = main_r["iterated"]
+    roofline = {"kernel": "subspace_batch" if iterated else "jacobi_persistent", **{k: main_r["rl"]["jacobi"][k] for k in
                                                    ("bound", "achieved", "peak", "unit", "frac")},
-                "frac_unpacked": round(main_r["rl"]["jacobi"]["achieved"] / PEAK_FP32_UNPACKED_TFLOPS, 4),
-                "traffic": traffic_bytes(B), "avg_launch_ms": round(avg["jacobi"], 4),
+                "traffic": traffic_bytes(B) if iterated else None, "avg_launch_ms": round(avg["jacobi"], 4),
                 "flops_per_launch": main_r["jflops"], "bins_per_launch": B * F}
+    if not iterated:
+        roofline["frac_unpacked"] = round(
+            main_r["rl"]["jacobi"]["achieved"] / PEAK_FP32_UNPACKED_TFLOPS, 4)
     conv_all = main_r["conv"]
     out = {
         "metric": "GSVD-MUSIC blocks/s (60ch, 257 bins, 1368 dirs) + p50/p99 served latency",
@@ -783,8 +800,10 @@ def main() -> int:
         "config": {"workload": w.name, "M": M, "F": F, "T": T, "D": D, "Ns": Ns, "p": 2,
                    "blocks_per_step": B, "path": "ssl_localize_batch",
                    "mfma_inputs": args.prec, "whitening": "fp64",
-                   "svd": "fp32 one-sided Jacobi (two-QR preconditioned), stopped at the "
-                          "signal / noise split",
+                   "svd": ("signal subspace by block subspace iteration, FP32 then FP64 MFMA"
+                           if iterated else
+                           "fp32 one-sided Jacobi (two-QR preconditioned), stopped at the "
+                           "signal / noise split"),
                    "projection": ("eq.5 through the signal subspace, FP64 MFMA"
                                   if Ns <= 3 else
                                   f"eq.5 over the noise vectors, {args.prec} MFMA")},
@@ -828,7 +847,7 @@ def main() -> int:
                   "steer_roofline": r["rl"]["steer"], "corr_roofline": r["rl"]["corr"],
                   "kind": f"{c} MFMA inputs for the correlation (FP32 accumulation) and a {c} "
                           f"steering table for the projection (through the signal subspace, "
-                          f"FP64), FP64 whitening, FP32 Jacobi: batched, and one block per call"}
+                          f"FP64): batched, and one block per call"}
     if f32 is not None:
         best = max([main_r] + list(sec.values()), key=lambda r: r["value"])
         out["speedup_vs_fp32_per_block"] = round(best["value"] / f32["per_block"], 3)

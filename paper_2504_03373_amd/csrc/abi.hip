@@ -172,6 +172,13 @@ int sub_full_for(ssl_ctx ctx, int p, bool batched)
     const int need = batched ? SSL_STOP_BATCH : SSL_STOP_LOCALIZE;
     return p == 2 && ctx->sub_stop >= need ? kSubFullSweeps : -1;
 }
+// Whether a block projected through the signal subspace gets it by block subspace iteration
+// (subspace.hip) instead of the Jacobi solve: more than 16 channels, and the solve may stop at the
+// subspace (the iteration knows no other singular vectors).
+bool use_iteration(ssl_ctx ctx, int M, bool sig, bool batched)
+{
+    return sig && subspace_class(M) != 0 && sub_full_for(ctx, 2, batched) >= 0;
+}
 int st_waves(ssl_ctx ctx, int M, int Ns, ssl_prec prec)
 {
     return ctx->steer_waves[steer_class_index(steer_class(M, Ns))][prec];
@@ -322,19 +329,30 @@ ssl_status localize_enqueue(ssl_ctx ctx, bool may_time, char *w, const LocalizeW
     });
     if (e != hipSuccess) return hip_fail(e, "corr launch");
     const bool gevd = use_gevd(ctx, K);
+    const bool sig = use_sig(ctx, prec, p, Ns, gevd);
+    const bool iter = use_iteration(ctx, M, sig, false);
     if (gevd) {
         e = run(SSL_K_WHITEN, [&] { return launch_gevd_whiten(K->Kisq, R, A, F, M, st); });
         if (e != hipSuccess) return hip_fail(e, "GEVD whitening launch");
+    } else if (K && iter) {
+        // the iteration applies K^{-1} and R in turn and forms A only where it gives up
     } else if (K) {
         e = run(SSL_K_WHITEN, [&] { return launch_whiten(K->Kinv, R, A, F, M, st); });
         if (e != hipSuccess) return hip_fail(e, "whiten launch");
     } else {
         A = R;                                   // SEVD-MUSIC: the decomposition of R itself
     }
-    const bool sig = use_sig(ctx, prec, p, Ns, gevd);
     ssl_c64 *Es = sig ? reinterpret_cast<ssl_c64 *>(w + L.off_es()) : nullptr;
     ssl_c128 *Esl = sig ? reinterpret_cast<ssl_c128 *>(w + L.off_es() + L.bEs) : nullptr;
     e = run(SSL_K_JACOBI, [&] {
+        if (iter) {
+            const hipError_t le = launch_subspace(K ? K->Kinv : nullptr, K ? K->status : nullptr, R,
+                                                  A, F, M, Ns, stt, Es, Esl, st);
+            if (le != hipSuccess) return le;
+            return launch_jacobi(A, K ? K->status : nullptr, F, M, Ns, SSL_DEFAULT_SWEEPS,
+                                 jac_lanes(ctx, M), nullptr, nullptr, stt, nullptr, st, nullptr,
+                                 sub_full_for(ctx, p, false), Es, Esl, true);
+        }
         // through the signal subspace the noise vectors are neither formed nor stored
         return launch_svd(ctx, A, K ? K->status : nullptr, F, M, Ns, SSL_DEFAULT_SWEEPS,
                           sig ? nullptr : En, nullptr, stt, nullptr, st, nullptr,
@@ -1083,6 +1101,7 @@ ssl_status ssl_sliding_localize(ssl_sliding s, ssl_noise K, const void *H, ssl_p
 // ------------------------------------------------------------------------------------------------
 namespace {
 
+constexpr int kIterClass = 1000;     // offset of the subspace iteration's classes in the item lists
 constexpr int kJacobiQueues = 4;     // counters[0..3]: work queues of Jacobi classes 8/16/32/64
 
 int jacobi_queue(int cls) { return cls == 8 ? 0 : cls == 16 ? 1 : cls == 32 ? 2 : 3; }
@@ -1096,6 +1115,9 @@ struct Seg {
 // Launch plan of one batch shape: per kernel, contiguous runs of items sharing a size class.
 struct Plan {
     std::vector<Seg> corr, whiten, jac, steer;
+    // blocks solved by subspace iteration: its launches by subspace class, and the Jacobi launches
+    // over the same items, by Jacobi class, for the bins it leaves
+    std::vector<Seg> iter, pending;
     int nblocks = 0, n_items = 0, max_dc = 0, max_fc = 0;
     std::vector<Seg> gevd;                 // (block, bin) items of GEVD-MUSIC blocks, by class
     int nsmax = 1;                         // largest Ns of the blocks projected by steer_sig
@@ -1239,6 +1261,20 @@ hipError_t enqueue_batch(ssl_ctx ctx, const Plan &P, const BlockDev *blk, const 
                                        ctx->jac_lanes[jacobi_class_index(s.cls)],
                                        SSL_DEFAULT_SWEEPS, ctx->counters + jacobi_queue(s.cls),
                                        s.extra, st, sub_full_for(ctx, 2, true));
+        });
+        if (e != hipSuccess) return e;
+    }
+    for (const Seg &s : P.pending) {
+        e = timed(ctx, SSL_K_JACOBI, st, [&] {
+            for (const Seg &i : P.iter) {
+                if (i.start < s.start || i.start >= s.start + s.count) continue;
+                const hipError_t le = launch_subspace_batch(blk, l_jac + i.start, i.count, i.cls, st);
+                if (le != hipSuccess) return le;
+            }
+            return launch_jacobi_pending(blk, l_jac + s.start, s.count, s.cls,
+                                         ctx->jac_lanes[jacobi_class_index(s.cls)],
+                                         SSL_DEFAULT_SWEEPS, s.extra, sub_full_for(ctx, 2, true),
+                                         st);
         });
         if (e != hipSuccess) return e;
     }
@@ -1616,6 +1652,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
     size_t ws_total = 0;
     int64_t n_items = 0;
     std::vector<char> sigb(nblocks);        // block projected through the signal subspace
+    std::vector<char> iterb(nblocks);       // its signal vectors by subspace iteration
     int nsmax = 1;
     std::vector<int64_t> key;
     key.reserve(10 + 6 * (size_t)nblocks);
@@ -1653,6 +1690,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         }
         key.push_back(d.K ? (use_gevd(ctx, d.K) ? 2 : 1) : 0);
         sigb[b] = use_sig(ctx, prec, p, d.Ns, use_gevd(ctx, d.K)) ? 1 : 0;
+        iterb[b] = use_iteration(ctx, d.M, sigb[b], true) ? 1 : 0;
         if (sigb[b]) nsmax = std::max(nsmax, d.Ns);
         key.push_back(sigb[b]);
         const size_t F = d.F, M = d.M, D = (size_t)d.n_az * d.n_el, Nn = d.M - d.Ns;
@@ -1750,7 +1788,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         B.conv = d.conv;
         c_corr[b] = corr_class(d.M);
         c_wh[b] = whiten_class(d.M);
-        c_jac[b] = jacobi_class(d.M);
+        c_jac[b] = iterb[b] ? kIterClass + subspace_class(d.M) : jacobi_class(d.M);
         c_st[b] = steer_class(d.M, d.Ns);
         Fs[b] = d.F;
         plan.max_dc = std::max(plan.max_dc, (int)((D + binsum_threads() - 1) / binsum_threads()));
@@ -1775,7 +1813,8 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         std::vector<std::vector<int>> members;
         std::map<std::tuple<int, const void *>, int> group_of;
         for (int b = 0; b < nblocks; ++b) {
-            if (!hb[b].Kinv || hb[b].Kisq) {          // SEVD / GEVD block: not whitened here
+            // SEVD and GEVD blocks and those of the subspace iteration are not whitened here
+            if (!hb[b].Kinv || hb[b].Kisq || iterb[b]) {
                 key.push_back(-1);
                 continue;
             }
@@ -1791,7 +1830,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         }
         std::vector<int> classes;
         for (int b = 0; b < nblocks; ++b)
-            if (hb[b].Kinv && !hb[b].Kisq) classes.push_back(c_wh[b]);
+            if (hb[b].Kinv && !hb[b].Kisq && !iterb[b]) classes.push_back(c_wh[b]);
         std::sort(classes.begin(), classes.end());
         classes.erase(std::unique(classes.begin(), classes.end()), classes.end());
         int2 *out = hl + n_items;
@@ -1823,7 +1862,24 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             plan.whiten.push_back(sg);
         }
     }
-    build_list(c_jac, Fs, hl + 2 * n_items, plan.jac);
+    {
+        // Jacobi items by class, then those of the subspace iteration by its classes: 32 goes with
+        // Jacobi class 32 and 48, 60, 64 with 64, each a contiguous run of items
+        std::vector<Seg> segs;
+        build_list(c_jac, Fs, hl + 2 * n_items, segs);
+        for (Seg &sg : segs) {
+            if (sg.cls < kIterClass) {
+                plan.jac.push_back(sg);
+                continue;
+            }
+            sg.cls -= kIterClass;
+            plan.iter.push_back(sg);
+            const int jc = sg.cls == 32 ? 32 : 64;
+            if (plan.pending.empty() || plan.pending.back().cls != jc)
+                plan.pending.push_back(Seg{jc, sg.start, 0, 0});
+            plan.pending.back().count += sg.count;
+        }
+    }
     {
         // steering groups (first-appearance order), then (group, bin) items by ascending class
         int2 *hg = hl + 4 * n_items;
@@ -1865,9 +1921,10 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
                 if (sg.count) plan.steer.push_back(sg);
             }
     }
-    for (Seg &sg : plan.jac)
-        sg.extra = std::min(sg.count, ctx->cu_count * jacobi_persistent_wg_per_cu(
-                                                         sg.cls, ctx->jac_lanes[jacobi_class_index(sg.cls)]));
+    for (std::vector<Seg> *v : {&plan.jac, &plan.pending})
+        for (Seg &sg : *v)
+            sg.extra = std::min(sg.count, ctx->cu_count * jacobi_persistent_wg_per_cu(
+                                              sg.cls, ctx->jac_lanes[jacobi_class_index(sg.cls)]));
     for (Seg &sg : plan.steer) {
         sg.waves = ctx->steer_waves[steer_class_index(sg.cls)][prec];
         const int rows = steer_rows_per_block(sg.waves);

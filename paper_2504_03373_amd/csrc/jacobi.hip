@@ -59,7 +59,7 @@
 //  * epilogue: sigma from the column norms, stable descending rank sort (ties: lower column
 //    first), U = Q U_R with each group taking its columns through all reflectors in registers,
 //    E_n = sorted columns Ns..M-1 of U, written column-major per bin.
-#include "ssl_internal.h"
+#include "signal_out.h"
 
 #include <atomic>
 
@@ -1364,78 +1364,8 @@ __device__ __forceinline__ void jacobi_bin(float2 *__restrict__ Af, int kst, int
             const int c = e / MP, r = e % MP;
             if (r < M) Esf[c * M + r] = ok ? sigvec(c, r) : make_float2(0.f, 0.f);
         }
-    if (Esf != nullptr && Lf != nullptr && Ns <= 3 && tid < 64) {
-        // Gram matrix of the stored signal vectors in FP64 (wave 0, one row per lane), then the
-        // inverse of its Cholesky factor on lane 0
-        const int r = tid;
-        double2 e[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const float2 v = (ok && k < Ns && r < M) ? sigvec(k, r) : make_float2(0.f, 0.f);
-            e[k] = make_double2(v.x, v.y);
-        }
-        double gr[6], gi[6];                       // Gamma_st = e_s^H e_t, index t (t + 1) / 2 + s
-#pragma unroll
-        for (int t = 0; t < 3; ++t)
-#pragma unroll
-            for (int s2 = 0; s2 <= t; ++s2) {
-                const int i = t * (t + 1) / 2 + s2;
-                double a = fma(e[s2].x, e[t].x, e[s2].y * e[t].y);
-                double b = fma(e[s2].x, e[t].y, -e[s2].y * e[t].x);
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    a += __shfl_xor(a, o);
-                    b += __shfl_xor(b, o);
-                }
-                gr[i] = a;
-                gi[i] = b;
-            }
-        if (r == 0) {
-            double2 out[6];
-#pragma unroll
-            for (int i = 0; i < 6; ++i) out[i] = make_double2(0.0, 0.0);
-            // Gamma = L L^H: L_t0 = conj(Gamma_0t) / L00, ... (lower rows t, columns s)
-            const double l00 = sqrt(gr[0]);
-            bool pd = ok && gr[0] > 0.0;
-            double2 l10 = make_double2(0.0, 0.0), l20 = l10, l21 = l10;
-            double l11 = 1.0, l22 = 1.0;
-            if (Ns >= 2 && pd) {
-                l10 = make_double2(gr[1] / l00, -gi[1] / l00);
-                const double d = gr[2] - (l10.x * l10.x + l10.y * l10.y);
-                pd = d > 0.0;
-                l11 = sqrt(fmax(d, 0.0));
-            }
-            if (Ns >= 3 && pd) {
-                l20 = make_double2(gr[3] / l00, -gi[3] / l00);
-                // Gamma_21 = conj(Gamma_12) minus L20 conj(L10), over L11
-                const double2 g21 = make_double2(gr[4], -gi[4]);
-                const double2 t21 = make_double2(g21.x - (l20.x * l10.x + l20.y * l10.y),
-                                                 g21.y - (l20.y * l10.x - l20.x * l10.y));
-                l21 = make_double2(t21.x / l11, t21.y / l11);
-                const double d = gr[5] - (l20.x * l20.x + l20.y * l20.y) -
-                                 (l21.x * l21.x + l21.y * l21.y);
-                pd = d > 0.0;
-                l22 = sqrt(fmax(d, 0.0));
-            }
-            if (pd) {
-                const double i00 = 1.0 / l00, i11 = 1.0 / l11, i22 = 1.0 / l22;
-                // inverse of the lower triangular L, column by column
-                const double2 i10 = make_double2(-l10.x * i00 * i11, -l10.y * i00 * i11);
-                const double2 i21 = make_double2(-l21.x * i11 * i22, -l21.y * i11 * i22);
-                const double2 s20 = make_double2(l20.x * i00 + (l21.x * i10.x - l21.y * i10.y),
-                                                 l20.y * i00 + (l21.x * i10.y + l21.y * i10.x));
-                const double2 i20 = make_double2(-s20.x * i22, -s20.y * i22);
-                out[0] = make_double2(i00, 0.0);
-                out[1] = i10;
-                out[2] = make_double2(i11, 0.0);
-                out[3] = i20;
-                out[4] = i21;
-                out[5] = make_double2(i22, 0.0);
-            }
-#pragma unroll
-            for (int i = 0; i < 6; ++i) Lf[i] = out[i];
-        }
-    }
+    if (Esf != nullptr && Lf != nullptr && Ns <= 3 && tid < 64)
+        write_signal_factor(sigvec, ok, Ns, M, tid, Lf);
     if (sigf != nullptr)
         for (int k = tid; k < M; k += NT) sigf[k] = ok ? sig[perm[k]] : 0.0f;
     if (Uf != nullptr)                                     // all M sorted columns (identity if failed)
@@ -1454,15 +1384,17 @@ __device__ __forceinline__ void jacobi_bin(float2 *__restrict__ Af, int kst, int
     }
 }
 
-// one workgroup per bin of one block
+// one workgroup per bin of one block; pending: only the bins that the subspace iteration left
+// (status SSL_BIN_PENDING)
 template <int MP, int G>
 __global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS)) void jacobi_svd(
     float2 *__restrict__ A, const int32_t *__restrict__ kstatus, int M, int Ns, int max_sweeps,
     float2 *__restrict__ En, float *__restrict__ sigma, int32_t *__restrict__ bin_status,
     int32_t *__restrict__ conv, float2 *__restrict__ U, int sub_full, float2 *__restrict__ Es,
-    double2 *__restrict__ Esl)
+    double2 *__restrict__ Esl, bool pending)
 {
     const int f = blockIdx.x;
+    if (pending && bin_status[f] != SSL_BIN_PENDING) return;    // uniform: the bin is solved
     jacobi_bin<MP, G>(A + (size_t)f * M * M, kstatus ? kstatus[f] : SSL_BIN_OK, M, Ns, max_sweeps,
                       En ? En + (size_t)f * (M - Ns) * M : nullptr,
                       sigma ? sigma + (size_t)f * M : nullptr,
@@ -1501,6 +1433,49 @@ __attribute__((amdgpu_waves_per_eu(JacobiCfg<MP, G>::WAVES_PER_EU))) void jacobi
                           nullptr, B.p == 2 ? sub_full : -1,
                           B.Es ? B.Es + (size_t)f * Ns * M : nullptr,
                           B.Esl ? B.Esl + 6 * (size_t)f : nullptr);
+    }
+}
+
+// After the subspace iteration over the same items: solves the bins it left (status
+// SSL_BIN_PENDING), and runs the solve of the others of a block that asks for the Jacobi statistics
+// (conv) for those alone.  Workgroup w looks at the items w, w + grid, .. (one per lane of wave 0,
+// 64 at a time) and takes the ones to be solved in turn; few are, so most workgroups only look.
+template <int MP, int G>
+__global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS))
+__attribute__((amdgpu_waves_per_eu(JacobiCfg<MP, G>::WAVES_PER_EU))) void jacobi_pending(
+    const BlockDev *__restrict__ blk, const int2 *__restrict__ items, int n_items,
+    int max_sweeps, int sub_full)
+{
+    __shared__ unsigned long long todo_s;
+    const int tid = threadIdx.x, w = blockIdx.x, nw = gridDim.x;
+    const int mine = (n_items - w + nw - 1) / nw;               // items of this workgroup
+    for (int base = 0; base < mine; base += 64) {
+        __syncthreads();
+        if (tid < 64) {
+            bool need = false;
+            if (base + tid < mine) {
+                const int2 it = items[w + (size_t)(base + tid) * nw];
+                const BlockDev &B = blk[it.x];
+                need = B.conv != nullptr || B.status[it.y] == SSL_BIN_PENDING;
+            }
+            const unsigned long long m = __ballot(need);
+            if (tid == 0) todo_s = m;
+        }
+        __syncthreads();
+        unsigned long long todo = todo_s;
+        while (todo) {                                           // uniform
+            const int b = __ffsll(todo) - 1;
+            todo &= todo - 1;
+            const int2 it = items[w + (size_t)(base + b) * nw];
+            const BlockDev &B = blk[it.x];
+            const int f = it.y, M = B.M, Ns = B.Ns;
+            const bool stats = B.status[f] != SSL_BIN_PENDING;  // solved: statistics only
+            jacobi_bin<MP, G>(B.A + (size_t)f * M * M, B.kstatus ? B.kstatus[f] : SSL_BIN_OK, M,
+                              Ns, max_sweeps, nullptr, nullptr, stats ? nullptr : B.status + f,
+                              B.conv ? B.conv + 3 * (size_t)f : nullptr, nullptr, sub_full,
+                              stats ? nullptr : B.Es + (size_t)f * Ns * M,
+                              stats ? nullptr : B.Esl + 6 * (size_t)f);
+        }
     }
 }
 
@@ -1756,13 +1731,22 @@ __global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS)) void jacobi_warm(
 template <int MP, int G>
 hipError_t launch_cfg(ssl_c64 *A, const int32_t *kstatus, int F, int M, int Ns, int max_sweeps,
                       ssl_c64 *En, float *sigma, int32_t *bin_status, int32_t *conv, ssl_c64 *U,
-                      int sub_full, ssl_c64 *Es, ssl_c128 *Esl, hipStream_t st)
+                      int sub_full, ssl_c64 *Es, ssl_c128 *Esl, bool pending, hipStream_t st)
 {
     hipLaunchKernelGGL((jacobi_svd<MP, G>), dim3(F), dim3(JacobiCfg<MP, G>::THREADS), 0, st,
                        reinterpret_cast<float2 *>(A), kstatus, M, Ns, max_sweeps,
                        reinterpret_cast<float2 *>(En), sigma, bin_status, conv,
                        reinterpret_cast<float2 *>(U), sub_full, reinterpret_cast<float2 *>(Es),
-                       reinterpret_cast<double2 *>(Esl));
+                       reinterpret_cast<double2 *>(Esl), pending);
+    return hipGetLastError();
+}
+
+template <int MP, int G>
+hipError_t launch_pending(const BlockDev *blk, const int2 *items, int n_items, int max_sweeps,
+                          int grid, int sub_full, hipStream_t st)
+{
+    hipLaunchKernelGGL((jacobi_pending<MP, G>), dim3(grid), dim3(JacobiCfg<MP, G>::THREADS), 0, st,
+                       blk, items, n_items, max_sweeps, sub_full);
     return hipGetLastError();
 }
 
@@ -1835,12 +1819,25 @@ int jacobi_persistent_wg_per_cu(int cls, int lanes)
 
 hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int Ns, int max_sweeps,
                          int lanes, ssl_c64 *En, float *sigma, int32_t *bin_status, int32_t *conv,
-                         hipStream_t st, ssl_c64 *U, int sub_full, ssl_c64 *Es, ssl_c128 *Esl)
+                         hipStream_t st, ssl_c64 *U, int sub_full, ssl_c64 *Es, ssl_c128 *Esl,
+                         bool pending)
 {
     hipError_t e = hipErrorInvalidValue;
     dispatch(jacobi_class(M), lanes, [&]<int MP, int G>() {
         e = launch_cfg<MP, G>(A, kstatus, F, M, Ns, max_sweeps, En, sigma, bin_status, conv, U,
-                              sub_full, Es, Esl, st);
+                              sub_full, Es, Esl, pending, st);
+    });
+    return e;
+}
+
+hipError_t launch_jacobi_pending(const BlockDev *blk, const int2 *items, int n_items, int cls,
+                                 int lanes, int max_sweeps, int grid, int sub_full,
+                                 hipStream_t st)
+{
+    if (n_items <= 0) return hipSuccess;
+    hipError_t e = hipErrorInvalidValue;
+    dispatch(cls, lanes, [&]<int MP, int G>() {
+        e = launch_pending<MP, G>(blk, items, n_items, max_sweeps, grid, sub_full, st);
     });
     return e;
 }

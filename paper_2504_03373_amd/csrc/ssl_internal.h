@@ -12,6 +12,8 @@
 
 #define SSL_MAX_M 64
 #define SSL_DEFAULT_SWEEPS 20
+// Status of a bin between the subspace iteration and the Jacobi solve that follows it (internal)
+#define SSL_BIN_PENDING (-1)
 
 // Bin-sum chunking of the spectrum reduction: bins are summed in ascending order inside fixed
 // chunks of SSL_BINSUM_CHUNK bins, then the chunk partials in ascending chunk order.
@@ -153,6 +155,11 @@ __device__ __forceinline__ void gstore(T *p, T v)
 // same kernel variant whichever entry point schedules it.
 inline int corr_class(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 48 ? 48 : 64; }
 inline int whiten_class(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
+// M <= 16 stays with the Jacobi solve (0 here)
+inline int subspace_class(int M)
+{
+    return M <= 16 ? 0 : M <= 32 ? 32 : M <= 48 ? 48 : M <= 60 ? 60 : 64;
+}
 inline int jacobi_class(int M) { return M <= 8 ? 8 : M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 inline int steer_class(int M, int Ns)
 {
@@ -246,7 +253,19 @@ hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int N
                          int max_sweeps, int lanes, ssl_c64 *En, float *sigma,
                          int32_t *bin_status, int32_t *conv, hipStream_t st,
                          ssl_c64 *U = nullptr, int sub_full = -1, ssl_c64 *Es = nullptr,
-                         ssl_c128 *Esl = nullptr);
+                         ssl_c128 *Esl = nullptr, bool pending = false);
+// Signal vectors by block subspace iteration (subspace.hip, subspace_class(M) != 0, Ns <= 3): Es,
+// Esl and status SSL_BIN_OK, or status SSL_BIN_PENDING and A = K^{-1} R (A itself where Kinv is
+// null: R) for the Jacobi solve that has to follow -- launch_jacobi with pending, or
+// launch_jacobi_pending over the same items (whose blocks all have Es and p = 2).
+hipError_t launch_subspace(const ssl_c128 *Kinv, const int32_t *kstatus, const ssl_c64 *R,
+                           ssl_c64 *A, int F, int M, int Ns, int32_t *bin_status, ssl_c64 *Es,
+                           ssl_c128 *Esl, hipStream_t st);
+hipError_t launch_subspace_batch(const BlockDev *blk, const int2 *items, int n_items, int cls,
+                                 hipStream_t st);
+hipError_t launch_jacobi_pending(const BlockDev *blk, const int2 *items, int n_items, int cls,
+                                 int lanes, int max_sweeps, int grid, int sub_full,
+                                 hipStream_t st);
 // Full sweeps before the subspace phase (p = 2): none.  The signal set is chosen on the column
 // norms of X = R1^H, which the pivoted QR already grades, and only the pairs with a signal column
 // are ever visited (about 2.4 subspace sweeps instead of one full sweep and 1.3 subspace sweeps on
