@@ -10,130 +10,270 @@
 #include "ssl_internal.h"
 
 #include <atomic>
+#include <utility>
 
 namespace {
 
 constexpr double kPdRel = 9.094947017729282e-13;   // 2^-40: pivot floor relative to max_i K_ii
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b)
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// Lane L of each row of 16 lanes, to the whole row (DPP row_newbcast).
+template <int L>
+__device__ __forceinline__ double row_bcast(double v)
 {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + L, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + L, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
 
-// One workgroup per bin, the MP x MP complex128 matrix in registers: thread t owns column
-// j = t % MP of rows t / MP + (MP / 8) u, u < 8.  Step k with pivot p = W_kk (real for Hermitian
-// input):
-//   W_ij -= W_ik W_kj / p (i, j != k);  W_kj /= p;  W_ik = -W_ik / p;  W_kk = 1 / p.
-// Only the pivot row and column travel, through two LDS buffers alternating by step: the owners
-// post row and column k + 1 after their update, so a step costs one barrier.  After M steps
-// W = K^{-1}.  A pivot p <= 2^-40 max_i K_ii (or non-finite) marks the bin NOT_PD.
-template <int MP> constexpr int kFactorThreads = MP * MP / 8;
+// K^{-1} of one bin by in-place Gauss-Jordan elimination in blocks of 16 pivots, NW waves (M <= 16 NW),
+// wave w holding rows 16 w .. 16 w + 15 as NW tiles in the FP64 MFMA result layout (element e of lane l:
+// row l / 16 + 4 e, column l % 16).  Block step k with P = W_kk, after which W_kk = P^{-1}:
+//   W_kj = P^{-1} W_kj,  W_ij -= W_ik W_kj,  W_ik = -W_ik P^{-1}    (i, j != k).
+// Every wave posts its tile of block column k and wave k its rows; wave k inverts P alone (16 scalar
+// steps, one wave, no barrier: row and column of the pivot by lane broadcasts), wave j forms
+// W_kj and its W_jk, and each wave updates its tiles on v_mfma_f64_16x16x4f64 (four real products
+// per complex one).  A product with the explicit P^{-1} has an error of 2^-53 cond(P) that the update's
+// W_ik (large where P is) would amplify once more, so P^{-1} W_kj is corrected once by its residual
+// W_kj - P (P^{-1} W_kj), which leaves the error of a backward stable solve (P-bar error at cond(K) =
+// 1e8: 6e-3 without the correction, 2e-7 with it and with scalar pivots).  The scalar pivots are the Schur-complement diagonals d_k = L_kk^2 as without blocks; one
+// that is <= 2^-40 max_i K_ii or not finite marks the bin NOT_PD (the inverse is then zero).
+// Padding rows and columns (>= M) are zero and stay zero.
+//   Bound by the 16-step chain of the pivot blocks (about half of the cycles) and the FP64 matrix cores.
+// 257 bins of 60 channels: 52 us, five such sets in one launch 148 us, 11 of 16 and 8 channels 14 us
+// (122, 346 and 31 us with one barrier per scalar pivot and rank-1 updates on the vector ALU).
+template <int NW> struct FactorCfg {
+    static constexpr int THREADS = 64 * NW;
+    static constexpr int LD = 16 * NW + 1;         // LDS row stride, complex128
+};
 
-template <int MP>
+// One scalar step (pivot KK of the block) on a 16 x 16 tile of one wave.
+template <int KK>
+__device__ __forceinline__ void pivot_step(double2 (&a)[4], int lane, double thr, int m, bool &bad)
+{
+    constexpr int E = KK >> 2, G = (KK & 3) << 4;
+    if (KK >= m || bad) return;                        // uniform
+    const double2 rowk = make_double2(__shfl(a[E].x, G | (lane & 15)), __shfl(a[E].y, G | (lane & 15)));
+    const long long pb = __builtin_bit_cast(long long, a[E].x);
+    const int lo = __builtin_amdgcn_readlane((int)pb, G | KK);
+    const int hi = __builtin_amdgcn_readlane((int)(pb >> 32), G | KK);
+    const double p = __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+    if (!(p > thr && p < 1.7e308)) {                   // NaN and Inf too
+        bad = true;
+        return;
+    }
+    double ip = __builtin_amdgcn_rcp(p);
+    ip = fma(ip, fma(-p, ip, 1.0), ip);
+    ip = fma(ip, fma(-p, ip, 1.0), ip);
+    const double2 wk = make_double2(rowk.x * ip, rowk.y * ip);      // the pivot row, scaled
+    const bool colk = (lane & 15) == KK;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double2 c = make_double2(row_bcast<KK>(a[e].x), row_bcast<KK>(a[e].y));   // W_ik
+        // selects by component: on whole double2 values the compiler goes through scratch memory
+        const double gx = fma(-c.x, wk.x, fma(c.y, wk.y, a[e].x));
+        const double gy = fma(-c.x, wk.y, fma(-c.y, wk.x, a[e].y));
+        double nx = colk ? -c.x * ip : gx, ny = colk ? -c.y * ip : gy;
+        if (e == E) {
+            const bool rowe = (lane & 48) == G;
+            nx = rowe ? (colk ? ip : wk.x) : nx;
+            ny = rowe ? (colk ? 0.0 : wk.y) : ny;
+        }
+        a[e].x = nx;
+        a[e].y = ny;
+    }
+}
+template <int... KK>
+__device__ __forceinline__ void invert_tile(std::integer_sequence<int, KK...>, double2 (&a)[4],
+                                            int lane, double thr, int m, bool &bad)
+{
+    (pivot_step<KK>(a, lane, thr, m, bad), ...);
+}
+
+// out = init + sign * X y on one 16 x 16 complex tile, K = 16: x(q) the A operand of k-step q (row
+// lane % 16, column 4 q + lane / 16), y and out in the result layout, which is the B operand's too.
+template <class Init, class X>
+__device__ __forceinline__ void mul_add(Init &&init, X &&x, const double2 (&y)[4], double sign,
+                                        double2 (&out)[4])
+{
+    doublex4 re, im;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double2 v = init(e);
+        re[e] = v.x;
+        im[e] = v.y;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double2 v = x(q);
+        const double vx = sign * v.x, vy = sign * v.y;
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(vx, y[q].x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(vx, y[q].y, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(-vy, y[q].y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(vy, y[q].x, im, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = make_double2(re[e], im[e]);
+}
+
+template <int NW>
 __device__ __forceinline__ void noise_factor_bin(const double2 *__restrict__ Kf,
                                                  double2 *__restrict__ Wf,
                                                  int32_t *__restrict__ stf, int M)
 {
-    constexpr int RG = MP / 8;                     // row groups: rows of thread t are t / MP + RG u
-    __shared__ double2 colb[2][MP], rowb[2][MP];
-    __shared__ double diag_s[MP];
-    __shared__ double thr_s;
+    typedef FactorCfg<NW> C;
+    __shared__ double2 rowp[16 * C::LD];           // [pivot][column]: block row k, then P^{-1} of it
+    __shared__ double2 colp[16 * C::LD];           // [pivot][row]: block column k
+    __shared__ double dmax_s[NW];
     __shared__ int bad_s;
-    const int t = threadIdx.x;
-    const int j = t % MP, i0 = t / MP;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int kl = lane >> 4, cl = lane & 15;
 
-    double2 w[8];
+    double2 a[NW][4];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {                      // every load in flight first
-        const int i = i0 + RG * u;
-        w[u] = (i < M && j < M) ? gload(Kf + (size_t)i * M + j) : make_double2(0.0, 0.0);
-    }
+    for (int j = 0; j < NW; ++j)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int i = i0 + RG * u;
-        if (i == j) diag_s[i] = w[u].x;
-        if (j == 0) colb[0][i] = w[u];
-        if (i == 0) rowb[0][j] = w[u];
+        for (int e = 0; e < 4; ++e) {
+            const int r = 16 * wave + kl + 4 * e, c = 16 * j + cl;
+            a[j][e] = r < M && c < M ? gload(Kf + (size_t)r * M + c) : make_double2(0.0, 0.0);
+        }
+    // the largest diagonal entry (NaN if one is not finite: no pivot then passes)
+    double dm = 0.0;
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (j == wave && kl + 4 * e == cl && !(a[j][e].x <= dm)) dm = a[j][e].x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double v = __shfl_xor(dm, o);
+        if (dm == dm && !(v <= dm)) dm = v;            // a NaN on either side stays
     }
+    if (lane == 0) dmax_s[wave] = dm;
+    if (tid == 0) bad_s = 0;
     __syncthreads();
-    if (t == 0) {
-        double dm = 0.0;
-        bool fin = true;
-        for (int i = 0; i < M; ++i) {
-            const double d = diag_s[i];
-            fin = fin && isfinite(d);
-            dm = fmax(dm, d);
-        }
-        bad_s = (!(dm > 0.0) || !isfinite(dm) || !fin) ? 1 : 0;
-        thr_s = kPdRel * dm;
+    dm = 0.0;
+    bool fin = true;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        fin = fin && isfinite(dmax_s[w]);
+        dm = fmax(dm, dmax_s[w]);
     }
-    __syncthreads();
-    bool bad = bad_s != 0;
-    const double thr = thr_s;
-    for (int k = 0; k < M && !bad; ++k) {
-        const int b = k & 1;
-        const double p = rowb[b][k].x;                // every thread reads the same pivot
-        if (!isfinite(p) || p <= thr) {
-            bad = true;
-            break;
-        }
-        const double ip = 1.0 / p;
-        const double2 wkj = rowb[b][j];
-        double2 wik[8];                                // every pivot-column read in flight first
+    const double thr = kPdRel * dm;
+    bool bad = !fin || !(dm > 0.0);
+    const int nb = (M + 15) >> 4;
+    // In step k register tile j is column tile (j + k) mod NW: the loop stays rolled (straight-line code
+    // for every k would not fit the instruction cache), and the tiles are back in place at its end.
+#pragma unroll 1
+    for (int k = 0; k < NW; ++k) {
+        if (k < nb && !bad) {                          // uniform
+            const int ow = 16 * wave, ok = 16 * k;
+            // block column k from every wave, block row k from wave k
 #pragma unroll
-        for (int u = 0; u < 8; ++u) wik[u] = colb[b][i0 + RG * u];
-        // row i is the same for every lane of a wave (uniform branch); column j == k is one lane
-        // (a select).  Padding rows and columns hold zeros and stay zero: their w_kj / w_ik are 0.
+            for (int e = 0; e < 4; ++e) colp[cl * C::LD + ow + kl + 4 * e] = a[0][e];
+            if (wave == k) {
+                invert_tile(std::make_integer_sequence<int, 16>(), a[0], lane, thr, M - ok, bad);
+                if (bad && lane == 0) bad_s = 1;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + RG * u;
-            if (i == k) {
-                const double2 row = make_double2(w[u].x * ip, w[u].y * ip);
-                w[u] = (j == k) ? make_double2(ip, 0.0) : row;
-            } else {
-                const double2 tt = cmul(wik[u], wkj);
-                const double2 gen = make_double2(fma(-tt.x, ip, w[u].x), fma(-tt.y, ip, w[u].y));
-                const double2 col = make_double2(-w[u].x * ip, -w[u].y * ip);
-                w[u] = (j == k) ? col : gen;
+                for (int j = 0; j < NW; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        rowp[(kl + 4 * e) * C::LD + 16 * ((j + k) % NW) + cl] = a[j][e];
             }
-        }
-        if (k + 1 < M) {
+            __syncthreads();
+            bad = bad_s != 0;
+            double2 v[4];                              // V^T, element e: (pivot kl + 4 e, row cl)
+            if (wave != k && !bad) {
+                // W_kj = P^{-1} W_kj (j = wave), corrected by its residual
+                double2 r0[4], w[4], r[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + RG * u;
-                if (j == k + 1) colb[b ^ 1][i] = w[u];
-                if (i == k + 1) rowb[b ^ 1][j] = w[u];
+                for (int e = 0; e < 4; ++e) r0[e] = rowp[(kl + 4 * e) * C::LD + ow + cl];
+                auto inv = [&](int q) { return rowp[cl * C::LD + ok + 4 * q + kl]; };
+                mul_add([](int) { return make_double2(0.0, 0.0); }, inv, r0, 1.0, w);
+                mul_add([&](int e) { return r0[e]; },
+                        [&](int q) { return colp[(4 * q + kl) * C::LD + ok + cl]; }, w, -1.0, r);
+                mul_add([&](int e) { return w[e]; }, inv, r, 1.0, w);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)            // tile `wave` of the panel: read by this wave alone
+                    rowp[(kl + 4 * e) * C::LD + ow + cl] = w[e];
+                // V = W_ik P^{-1} (i = wave) as V^T = P^{-T} W_ik^T
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r0[e] = colp[(kl + 4 * e) * C::LD + ow + cl];
+                auto invt = [&](int q) { return rowp[(4 * q + kl) * C::LD + ok + cl]; };
+                mul_add([](int) { return make_double2(0.0, 0.0); }, invt, r0, 1.0, v);
             }
+            __syncthreads();
+            if (wave == k) {
+#pragma unroll
+                for (int j = 1; j < NW; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        a[j][e] = rowp[(kl + 4 * e) * C::LD + 16 * ((j + k) % NW) + cl];
+            } else if (!bad) {
+                auto cop = [&](int q) { return colp[(4 * q + kl) * C::LD + ow + cl]; };
+#pragma unroll
+                for (int j = 1; j < NW; ++j) {         // W_ij -= W_ik W_kj
+                    double2 y[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        y[q] = rowp[(4 * q + kl) * C::LD + 16 * ((j + k) % NW) + cl];
+                    mul_add([&](int e) { return a[j][e]; }, cop, y, -1.0, a[j]);
+                }
+                // W_ik = -V: the transpose through this wave's part of colp
+#pragma unroll
+                for (int e = 0; e < 4; ++e) colp[(kl + 4 * e) * C::LD + ow + cl] = v[e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double2 x = colp[cl * C::LD + ow + kl + 4 * e];
+                    a[0][e] = make_double2(-x.x, -x.y);
+                }
+            }
+            __syncthreads();                           // rowp and colp have been read
         }
-        __syncthreads();
+        if constexpr (NW > 1) {
+            double2 t[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] = a[0][e];
+#pragma unroll
+            for (int j = 0; j + 1 < NW; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[j][e] = a[j + 1][e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[NW - 1][e] = t[e];
+        }
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int i = i0 + RG * u;
-        if (i < M && j < M) gstore(Wf + (size_t)i * M + j, bad ? make_double2(0.0, 0.0) : w[u]);
-    }
-    if (t == 0) gstore(stf, (int32_t)(bad ? SSL_BIN_NOT_PD : SSL_BIN_OK));
+    for (int j = 0; j < NW; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = 16 * wave + kl + 4 * e, c = 16 * j + cl;
+            if (r < M && c < M)
+                gstore(Wf + (size_t)r * M + c, bad ? make_double2(0.0, 0.0) : a[j][e]);
+        }
+    if (tid == 0) gstore(stf, (int32_t)(bad ? SSL_BIN_NOT_PD : SSL_BIN_OK));
 }
 
 template <int MP>
-__global__ __launch_bounds__(kFactorThreads<MP>) void noise_factor(const double2 *__restrict__ K,
+__global__ __launch_bounds__((FactorCfg<MP / 16>::THREADS)) void noise_factor(const double2 *__restrict__ K,
                                                                     double2 *__restrict__ Kinv,
                                                                     int32_t *__restrict__ status,
                                                                     int M)
 {
     const int f = blockIdx.x;
-    noise_factor_bin<MP>(K + (size_t)f * M * M, Kinv + (size_t)f * M * M, status + f, M);
+    noise_factor_bin<MP / 16>(K + (size_t)f * M * M, Kinv + (size_t)f * M * M, status + f, M);
 }
 
 // Item (handle, bin) of a batched noise update.
 template <int MP>
-__global__ __launch_bounds__(kFactorThreads<MP>) void noise_factor_batch(
+__global__ __launch_bounds__((FactorCfg<MP / 16>::THREADS)) void noise_factor_batch(
     const NoiseUpdDev *__restrict__ h, const int2 *__restrict__ items)
 {
     const int2 it = items[blockIdx.x];
     const NoiseUpdDev &H = h[it.x];
     const int M = H.M, f = it.y;
-    noise_factor_bin<MP>(H.K + (size_t)f * M * M, H.Kinv + (size_t)f * M * M, H.status + f, M);
+    noise_factor_bin<MP / 16>(H.K + (size_t)f * M * M, H.Kinv + (size_t)f * M * M, H.status + f, M);
 }
 
 // K <- alpha K + (1 - alpha) Khat
@@ -185,7 +325,6 @@ __global__ void noise_load_c64(double2 *__restrict__ K, const float2 *__restrict
 // run; each block's R (complex64) is staged in LDS -- the next block's R is loaded into
 // registers under the current block's products -- and read as B operands, widened to FP64.
 // Padding rows, columns and k-steps (beyond M) are zero on both operands and never stored.
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 template <int MP> struct WhCfg {
     static constexpr int NT = MP / 16;          // row tiles = column tiles = waves
@@ -340,13 +479,13 @@ hipError_t launch_noise_factor(ssl_c128 *K, ssl_c128 *Kinv, int32_t *status, int
     const double2 *Kp = reinterpret_cast<const double2 *>(K);
     double2 *Wp = reinterpret_cast<double2 *>(Kinv);
     if (M <= 16)
-        hipLaunchKernelGGL(noise_factor<16>, dim3(F), dim3(kFactorThreads<16>), 0, st, Kp, Wp,
+        hipLaunchKernelGGL(noise_factor<16>, dim3(F), dim3(FactorCfg<1>::THREADS), 0, st, Kp, Wp,
                            status, M);
     else if (M <= 32)
-        hipLaunchKernelGGL(noise_factor<32>, dim3(F), dim3(kFactorThreads<32>), 0, st, Kp, Wp,
+        hipLaunchKernelGGL(noise_factor<32>, dim3(F), dim3(FactorCfg<2>::THREADS), 0, st, Kp, Wp,
                            status, M);
     else
-        hipLaunchKernelGGL(noise_factor<64>, dim3(F), dim3(kFactorThreads<64>), 0, st, Kp, Wp,
+        hipLaunchKernelGGL(noise_factor<64>, dim3(F), dim3(FactorCfg<4>::THREADS), 0, st, Kp, Wp,
                            status, M);
     return hipGetLastError();
 }
@@ -356,13 +495,13 @@ hipError_t launch_noise_factor_batch(const NoiseUpdDev *h, const int2 *items, in
 {
     if (n_items <= 0) return hipSuccess;
     if (cls == 16)
-        hipLaunchKernelGGL(noise_factor_batch<16>, dim3(n_items), dim3(kFactorThreads<16>), 0, st,
+        hipLaunchKernelGGL(noise_factor_batch<16>, dim3(n_items), dim3(FactorCfg<1>::THREADS), 0, st,
                            h, items);
     else if (cls == 32)
-        hipLaunchKernelGGL(noise_factor_batch<32>, dim3(n_items), dim3(kFactorThreads<32>), 0, st,
+        hipLaunchKernelGGL(noise_factor_batch<32>, dim3(n_items), dim3(FactorCfg<2>::THREADS), 0, st,
                            h, items);
     else
-        hipLaunchKernelGGL(noise_factor_batch<64>, dim3(n_items), dim3(kFactorThreads<64>), 0, st,
+        hipLaunchKernelGGL(noise_factor_batch<64>, dim3(n_items), dim3(FactorCfg<4>::THREADS), 0, st,
                            h, items);
     return hipGetLastError();
 }
