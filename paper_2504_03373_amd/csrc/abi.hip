@@ -1108,7 +1108,10 @@ int jacobi_queue(int cls) { return cls == 8 ? 0 : cls == 16 ? 1 : cls == 32 ? 2 
 
 struct Seg {
     int cls, start, count, extra;
-    int waves = 0;                         // projection: waves per workgroup
+    int waves = 0;                         // projection: waves per workgroup, or (signal subspace)
+                                           // direction tiles per workgroup
+                                           // (steer_sig_per_wg)
+    double columns = 0.0;                  // signal vectors per steering table, over its items
     bool sig = false;                      // projection: through the signal subspace
 };
 
@@ -1120,7 +1123,6 @@ struct Plan {
     std::vector<Seg> iter, pending;
     int nblocks = 0, n_items = 0, max_dc = 0, max_fc = 0;
     std::vector<Seg> gevd;                 // (block, bin) items of GEVD-MUSIC blocks, by class
-    int nsmax = 1;                         // largest Ns of the blocks projected by steer_sig
 };
 
 // Device tail of the descriptor buffer after the four item lists: steering groups (first, count)
@@ -1287,8 +1289,8 @@ hipError_t enqueue_batch(ssl_ctx ctx, const Plan &P, const BlockDev *blk, const 
     for (const Seg &s : P.steer) {
         e = timed(ctx, SSL_K_STEER, st, [&] {
             if (s.sig)
-                return launch_steer_sig_batch(blk, l_st + s.start, s.count, ga.groups, ga.gblocks,
-                                              s.extra, P.nsmax, prec, st);
+                return launch_steer_sig_batch(blk, l_st + s.start, s.count, ga.groups, ga.gblocks, s.cls,
+                                              s.extra, s.waves, prec, st);
             return launch_steer_batch(blk, l_st + s.start, s.count, ga.groups, ga.gblocks, s.cls,
                                       s.waves, s.extra, prec, st);
         });
@@ -1653,7 +1655,6 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
     int64_t n_items = 0;
     std::vector<char> sigb(nblocks);        // block projected through the signal subspace
     std::vector<char> iterb(nblocks);       // its signal vectors by subspace iteration
-    int nsmax = 1;
     std::vector<int64_t> key;
     key.reserve(10 + 6 * (size_t)nblocks);
     key.push_back(nblocks);
@@ -1691,7 +1692,6 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         key.push_back(d.K ? (use_gevd(ctx, d.K) ? 2 : 1) : 0);
         sigb[b] = use_sig(ctx, prec, p, d.Ns, use_gevd(ctx, d.K)) ? 1 : 0;
         iterb[b] = use_iteration(ctx, d.M, sigb[b], true) ? 1 : 0;
-        if (sigb[b]) nsmax = std::max(nsmax, d.Ns);
         key.push_back(sigb[b]);
         const size_t F = d.F, M = d.M, D = (size_t)d.n_az * d.n_el, Nn = d.M - d.Ns;
         const size_t nch = (F + SSL_BINSUM_CHUNK - 1) / SSL_BINSUM_CHUNK;
@@ -1711,7 +1711,6 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         ssl_set_error("batch too large");
         return SSL_ERR_ARG;
     }
-    key.push_back(nsmax);
     DeviceGuard dg(ctx->device);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t desc_bytes = align256(sizeof(BlockDev) * nblocks);
@@ -1740,7 +1739,6 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
     Plan plan;
     plan.nblocks = nblocks;
     plan.n_items = (int)n_items;
-    plan.nsmax = nsmax;
     std::vector<int> c_corr(nblocks), c_wh(nblocks), c_jac(nblocks), c_st(nblocks), Fs(nblocks);
     char *w = static_cast<char *>(ctx->ws);
     for (int b = 0; b < nblocks; ++b) {
@@ -1789,7 +1787,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         c_corr[b] = corr_class(d.M);
         c_wh[b] = whiten_class(d.M);
         c_jac[b] = iterb[b] ? kIterClass + subspace_class(d.M) : jacobi_class(d.M);
-        c_st[b] = steer_class(d.M, d.Ns);
+        c_st[b] = sigb[b] ? steer_sig_class(d.M) : steer_class(d.M, d.Ns);
         Fs[b] = d.F;
         plan.max_dc = std::max(plan.max_dc, (int)((D + binsum_threads() - 1) / binsum_threads()));
         plan.max_fc = std::max(plan.max_fc, (int)nch);
@@ -1901,6 +1899,9 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         }
         int at = 0;
         for (size_t g = 0; g < members.size(); ++g) {
+            // by Ns: the signal-subspace projection packs its column tiles with blocks of one Ns
+            std::stable_sort(members[g].begin(), members[g].end(),
+                             [&](int x, int y) { return hb[x].Ns < hb[y].Ns; });
             hg[g] = make_int2(at, (int)members[g].size());
             for (int b : members[g]) hgb[at++] = b;
         }
@@ -1915,6 +1916,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
                 sg.sig = kind == 1;
                 for (size_t g = 0; g < members.size(); ++g) {
                     if (c_st[first[g]] != c || sigb[first[g]] != kind) continue;
+                    for (int b : members[g]) sg.columns += (double)hb[b].Ns * hb[b].F;
                     for (int f = 0; f < hb[first[g]].F; ++f) out[pos++] = make_int2((int)g, f);
                 }
                 sg.count = pos - sg.start;
@@ -1933,6 +1935,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             if (c_st[b] == sg.cls && sigb[b] == (sg.sig ? 1 : 0))
                 dt = std::max(dt, sg.sig ? steer_sig_tiles(hb[b].D) : (hb[b].D + rows - 1) / rows);
         sg.extra = dt;
+        if (sg.sig) sg.waves = steer_sig_per_wg(sg.count, dt, sg.columns / sg.count, ctx->cu_count);
     }
 
     e = hipMemcpyAsync(ctx->bdesc_dev, ctx->bdesc_host, desc_bytes + list_bytes,

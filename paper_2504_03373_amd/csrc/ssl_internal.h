@@ -161,6 +161,11 @@ inline int subspace_class(int M)
     return M <= 16 ? 0 : M <= 32 ? 32 : M <= 48 ? 48 : M <= 60 ? 60 : 64;
 }
 inline int jacobi_class(int M) { return M <= 8 ? 8 : M <= 16 ? 16 : M <= 32 ? 32 : 64; }
+// of the signal-subspace projection (k-steps of its products)
+inline int steer_sig_class(int M)
+{
+    return M <= 16 ? 16 : M <= 32 ? 32 : M <= 48 ? 48 : M <= 60 ? 60 : 64;
+}
 inline int steer_class(int M, int Ns)
 {
     const int nn = M - Ns;                 // noise vectors = B columns, 16 per column tile
@@ -182,14 +187,15 @@ hipError_t launch_jacobi_batch(const BlockDev *blk, const int2 *items, int n_ite
                                hipStream_t st, int sub_full = -1);
 // eq.5 (p = 2) through the signal subspace, FP64 (steer_sig.hip): Es [F][Ns][M] and Esl [F][6]
 // from the Jacobi solve, H [F][D][M] complex64 or [F][D][2M] bf16 / fp16 pairs (hprec),
-// Ns <= 3; direction tiles of steer_sig_tiles(D).
+// Ns <= 3; direction tiles of steer_sig_tiles(D).  A group's blocks are listed by ascending Ns.
 int steer_sig_tiles(int D);
 hipError_t launch_steer_sig(const void *H, ssl_prec hprec, const ssl_c64 *Es,
                             const ssl_c128 *Esl, int F, int D, int M, int Ns,
                             const int32_t *bin_status, float *P, hipStream_t st);
+int steer_sig_per_wg(int64_t n_items, int n_tiles, double columns, int cus);
 hipError_t launch_steer_sig_batch(const BlockDev *blk, const int2 *items, int n_items,
-                                  const int2 *groups, const int *gblocks, int max_dtiles,
-                                  int nsmax, ssl_prec hprec, hipStream_t st);
+                                  const int2 *groups, const int *gblocks, int cls, int max_dtiles,
+                                  int per_wg, ssl_prec hprec, hipStream_t st);
 hipError_t launch_steer_batch(const BlockDev *blk, const int2 *items, int n_items,
                               const int2 *groups, const int *gblocks, int cls, int waves,
                               int max_dtiles, ssl_prec hprec, hipStream_t st);

@@ -13,15 +13,31 @@
 // both forms the same way).
 //
 // Workgroup = 4 waves x 16 directions of one bin; a wave keeps its 16 rows of H in registers
-// (complex64) and computes g for 16 columns at once on v_mfma_f64_16x16x4f64 -- the signal vectors
-// of 16 / Ns_max blocks sharing the steering table, staged in LDS -- with
+// (complex64) and computes g for a tile of up to 16 signal vectors, those of the next blocks sharing the
+// steering table (listed by Ns, their columns packed without gaps), staged in LDS, with
 //   Re g = sum a c + b d,   Im g = sum b c - a d     (h = a + ib, e = c + id, FP64 operands:
 // g_s = e_s^H h, the conjugate of h^H e_s, so that y = L^{-1} g with L from E_s^H E_s = L L^H),
 // on three real products instead of four (Gauss's trick): P1 = sum a c, P2 = sum b (-d),
 // P3 = sum (a + b)(c - d), Re g = P1 - P2, Im g = P3 - P1 - P2.  a + b and c - d are sums of two
 // FP32-representable values, exact in FP64 unless their exponents differ by more than 29.
-// The 16 x 16 result goes through LDS so that each lane finishes whole (direction, block) items.
+//   A tile takes v_mfma_f64_16x16x4f64 (64 cycles per k-step and product whatever it holds); a single
+// block, 1 to 3 columns, v_mfma_f64_4x4x4f64 (22 cycles for 4 columns).  Both give a column the same
+// bits (same k order and rounding, checked bit for bit), so a block's result does not depend on
+// the tile it shares.  A k-step holds elements 8 p + 2
+// (l / 16) + h, h = 0 or 1, so that a lane loads the two of k-steps 2 p and 2 p + 1 at once (16
+// bytes) where rows are 16-byte aligned.
+//   FP64 vector instructions do not run beside FP64 MFMAs (measured: each adds its own 4.5 cycles), so
+// the epilogue is kept short: reciprocal by Newton steps instead of a division, one lane per
+// (block, direction) with consecutive lanes on consecutive directions.
+//   Measured (60 channels, 257 bins, 1368 directions): one block 47 us (68 us with 16-column tiles and
+// 8-byte loads; the 169 MB table alone takes 34 us at copy rate), 128 blocks 0.78 ms (as before; the
+// FP64 MFMAs alone take 0.43 ms).  Blocks of 8, 16, 32 and 60 channels, 257 and 513 bins, one to three
+// sources, 96 in all: 0.95 ms against 1.25 ms with column tiles spaced for the largest Ns and as
+// many k-steps as 64 channels need.
 #include "ssl_internal.h"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -30,8 +46,6 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kRows = 16 * kWaves;          // directions per workgroup
-constexpr int kCols = 16;                   // signal vectors per MFMA tile
-constexpr int kKq = SSL_MAX_M / 4;          // k-steps of 4 complex elements at M = 64
 constexpr int kEs = SSL_MAX_M + 2;          // complex64 stride of a staged signal vector
 constexpr int kChunk = kThreads;            // blocks whose descriptors are held in LDS at once
 
@@ -40,171 +54,320 @@ constexpr int kChunk = kThreads;            // blocks whose descriptors are held
 struct TabF32 {
     typedef float2 W;
     static __device__ __forceinline__ float2 get(const W *p) { return gload(p); }
+    static __device__ __forceinline__ void get2(const W *p, float2 &x, float2 &y)
+    {
+        const float4 v = gload(reinterpret_cast<const float4 *>(p));
+        x = make_float2(v.x, v.y);
+        y = make_float2(v.z, v.w);
+    }
 };
 struct TabBF16 {
     typedef unsigned int W;
     static __device__ __forceinline__ float2 get(const W *p)
     {
-        const unsigned int w = gload(p);
+        return wide(gload(p));
+    }
+    static __device__ __forceinline__ float2 wide(unsigned int w)
+    {
         return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+    }
+    static __device__ __forceinline__ void get2(const W *p, float2 &x, float2 &y)
+    {
+        const uint2 v = gload(reinterpret_cast<const uint2 *>(p));
+        x = wide(v.x);
+        y = wide(v.y);
     }
 };
 struct TabF16 {
     typedef unsigned int W;
     static __device__ __forceinline__ float2 get(const W *p)
     {
-        const unsigned int w = gload(p);
+        return wide(gload(p));
+    }
+    static __device__ __forceinline__ float2 wide(unsigned int w)
+    {
         return make_float2((float)__builtin_bit_cast(_Float16, (unsigned short)(w & 0xffffu)),
                            (float)__builtin_bit_cast(_Float16, (unsigned short)(w >> 16)));
     }
+    static __device__ __forceinline__ void get2(const W *p, float2 &x, float2 &y)
+    {
+        const uint2 v = gload(reinterpret_cast<const uint2 *>(p));
+        x = wide(v.x);
+        y = wide(v.y);
+    }
 };
 
-// One workgroup: directions d0 .. d0 + 63 of bin f for nb blocks sharing the table Hf (the bin's
-// [D][M] complex64 rows).  blk(i, Es, L, ns, ok, P) gives block i's signal vectors and L^{-1} of
-// the bin, its Ns, whether the bin is valid, and its P row of the bin.
-template <class Tab, class BlockAt>
-__device__ __forceinline__ void sig_tile(const typename Tab::W *__restrict__ Hf, int D, int M,
-                                         int d0, int nb, int nsmax, BlockAt &&blk)
+// Orders a wave's LDS accesses: the hardware completes one wave's in issue order, so only the compiler
+// has to be kept from moving them across.
+__device__ __forceinline__ void wave_lds_sync()
 {
-    __shared__ float2 Es[2][kCols * kEs];                    // signal vectors, by tile parity
-    __shared__ double2 Ls[2][kCols][6];
-    __shared__ double2 Gs[kWaves][16 * kCols];
-    __shared__ float *Pp[kChunk];                            // per block of the chunk
-    __shared__ const float2 *Ep[kChunk];
-    __shared__ const double2 *Lp[kChunk];
-    __shared__ int Nsb[kChunk];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// 1/x for normal x > 0: hardware estimate and two Newton steps
+__device__ __forceinline__ double rcp_refined(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+
+// The blocks of a column tile: t1 with one signal vector, then t2 with two, then t3 with three.
+struct Tile {
+    int t1, t2, t3;
+    __device__ __forceinline__ int blocks() const { return t1 + t2 + t3; }
+    __device__ __forceinline__ int ns(int b) const { return b < t1 ? 1 : b < t1 + t2 ? 2 : 3; }
+    __device__ __forceinline__ int column(int b) const      // first column of block b
+    {
+        return b < t1 ? b : b < t1 + t2 ? 2 * b - t1 : 3 * b - 2 * t1 - t2;
+    }
+    __device__ __forceinline__ int block(int j) const       // block of column j (>= blocks() beyond)
+    {
+        const int r = j - t1, q = r - 2 * t2;
+        return r < 0 ? j : q < 0 ? t1 + (r >> 1) : t1 + t2 + q / 3;
+    }
+};
+
+// One workgroup: nd tiles of 64 directions of bin f from tile0 on, for nb blocks sharing the table Hf
+// (the bin's [D][M] rows), in ascending order of Ns.  blk(i, Es, L, ns, ok, P) gives block i's signal
+// vectors and L^{-1} of the bin, its Ns, whether the bin is valid, and its P row of the bin.  COLS:
+// columns of a tile (16, or 4 for a single block); KQ: k-steps (at least those of M; the ones beyond
+// hold zeros).  LOOP: nd tiles, else one.  Column tiles pass through two LDS stages; with LOOP, where two
+// column tiles hold all blocks, they stay there for every direction tile, whose rows are loaded under
+// the previous one's products, and the waves run without barriers.
+template <class Tab, int COLS, int KQ, bool LOOP, class BlockAt>
+__device__ __forceinline__ void sig_tile(const typename Tab::W *__restrict__ Hf, int D, int M,
+                                         int tile0, int nd, int nb, BlockAt &&blk)
+{
+    constexpr int CHUNK = COLS < 16 ? 4 : kChunk;
+    constexpr int GS = COLS + 1;                             // complex128 stride of a direction
+    __shared__ float2 Es[2][COLS * kEs];                     // signal vectors, by tile parity
+    __shared__ double2 Ls[2][COLS][6];
+    __shared__ double2 Gs[kWaves][16 * GS];
+    __shared__ float *Pp[CHUNK];                             // per block of the chunk
+    __shared__ const float2 *Ep[CHUNK];
+    __shared__ const double2 *Lp[CHUNK];
+    __shared__ int Nsb[CHUNK];                               // Ns, 0 for a failed bin
     __shared__ double nrm_s[kRows];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int KQ = (M + 3) >> 2;
-    const int bpt = kCols / nsmax;                           // blocks per tile
+    const int kl = lane >> 4;
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    // k-steps: pairs (2 p, 2 p + 1) over elements 8 p .. 8 p + 7; a remainder of up to 4 elements takes
+    // one k-step (element 8 p + l / 16)
+    const int P8 = M >> 3, rem = M & 7;
+    const bool lone = rem != 0 && rem <= 4;                  // the last k-step is a single one
+    auto slot = [&](int m) {                                 // LDS position of element m of a column
+        const int p = m >> 3, w = m & 7;
+        return lone && p == P8 ? 8 * p + w : 8 * p + ((w & 1) << 2) + (w >> 1);
+    };
 
-    // this lane's A operands: row (lane & 15), complex elements 4 q + (lane >> 4)
-    const int row = d0 + 16 * wave + (lane & 15);
-    const typename Tab::W *hrow = Hf + (size_t)(row < D ? row : 0) * M;
-    float2 ha[kKq];
-    double hn = 0.0;
+    // this lane's A operands of k-steps q: row (lane & 15) of the wave's 16 directions
+    const bool pair = (M & 1) == 0 && (reinterpret_cast<size_t>(Hf) & (2 * sizeof(*Hf) - 1)) == 0;
+    auto load_h = [&](int tile, float2 (&h)[KQ + (KQ & 1)]) {
+        const int row = tile * kRows + 16 * wave + (lane & 15);
+        const typename Tab::W *hrow = Hf + (size_t)(row < D ? row : 0) * M;
 #pragma unroll
-    for (int q = 0; q < kKq; ++q) {
-        const int m = 4 * q + (lane >> 4);
-        ha[q] = (q < KQ && m < M && row < D) ? Tab::get(hrow + m) : make_float2(0.f, 0.f);
-        hn = fma((double)ha[q].x, (double)ha[q].x, fma((double)ha[q].y, (double)ha[q].y, hn));
-    }
-    hn += __shfl_xor(hn, 16);
-    hn += __shfl_xor(hn, 32);
-    if (lane < 16) nrm_s[16 * wave + lane] = hn;
+        for (int p = 0; p < (KQ + 1) / 2; ++p) {
+            const int m = 8 * p + 2 * kl;
+            float2 x = make_float2(0.f, 0.f), y = x;
+            if (p < P8 || (p == P8 && rem > 4)) {            // uniform
+                if (pair) {
+                    if (m < M && row < D) Tab::get2(hrow + m, x, y);
+                } else if (row < D) {
+                    if (m < M) x = Tab::get(hrow + m);
+                    if (m + 1 < M) y = Tab::get(hrow + m + 1);
+                }
+            } else if (p == P8 && lone) {
+                if (8 * p + kl < M && row < D) x = Tab::get(hrow + 8 * p + kl);
+            }
+            h[2 * p] = x;
+            h[2 * p + 1] = y;
+        }
+    };
 
-    // One tile's operands into registers: thread x < kCols * SSL_MAX_M (kPer per thread) holds
-    // element m of column j = block j / nsmax, vector j % nsmax (zero if absent); threads below
-    // kCols * 6 hold one L^{-1} entry.  Loaded one tile ahead, so that the loads are in flight
-    // under the current tile's products and epilogue; stored to the other parity's buffers.
-    constexpr int kPer = kCols * SSL_MAX_M / kThreads;
+    // One column tile's operands into registers: a wave holds every kWaves-th column, one element per
+    // lane (zero if absent); threads below COLS * 6 hold one L^{-1} entry.  Loaded
+    // one tile ahead, so that the loads are in flight under the current tile's products and
+    // epilogue; stored to the other parity's buffers.
+    static_assert(SSL_MAX_M == 64, "a lane per element of a column");
+    constexpr int kPer = COLS / kWaves;
     float2 ev[kPer];
     double2 lv;
-    auto load_tile = [&](int c0, int nt) {                   // c0: first block, chunk-relative
+    auto load_tile = [&](int c0, const Tile &t) {            // c0: first block, chunk-relative
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const int x = tid + kThreads * i;
-            const int j = x / SSL_MAX_M, m = x - j * SSL_MAX_M;
-            const int bi = j / nsmax, s = j - bi * nsmax;
-            ev[i] = (bi < nt && m < M && s < Nsb[c0 + bi]) ? gload(Ep[c0 + bi] + (size_t)s * M + m)
-                                                           : make_float2(0.f, 0.f);
+            const int j = uwave + kWaves * i, m = lane;
+            const int bi = t.block(j), s = j - t.column(bi);
+            ev[i] = (bi < t.blocks() && m < M && Nsb[c0 + bi] > 0)
+                        ? gload(Ep[c0 + bi] + (size_t)s * M + m)
+                        : make_float2(0.f, 0.f);
         }
         const int bi = tid / 6, k = tid - bi * 6;
-        lv = (tid < kCols * 6 && bi < nt && Nsb[c0 + bi] > 0) ? gload(Lp[c0 + bi] + k)
-                                                              : make_double2(0.0, 0.0);
+        lv = (tid < COLS * 6 && bi < t.blocks() && Nsb[c0 + bi] > 0) ? gload(Lp[c0 + bi] + k)
+                                                                     : make_double2(0.0, 0.0);
     };
     auto store_tile = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const int x = tid + kThreads * i;
-            const int j = x / SSL_MAX_M, m = x - j * SSL_MAX_M;
-            Es[buf][j * kEs + m] = ev[i];
+            const int j = uwave + kWaves * i;
+            Es[buf][j * kEs + slot(lane)] = ev[i];
         }
-        if (tid < kCols * 6) Ls[buf][tid / 6][tid % 6] = lv;
+        if (tid < COLS * 6) Ls[buf][tid / 6][tid % 6] = lv;
     };
 
-    for (int h0 = 0; h0 < nb; h0 += kChunk) {               // chunks of the blocks' descriptors
-        const int nc = min(kChunk, nb - h0);
-        __syncthreads();                                     // the previous chunk is finished
-        if (tid < nc) {
-            const float2 *e;
-            const double2 *L;
-            float *P;
-            int ns = 0;
-            bool ok = false;
-            blk(h0 + tid, e, L, ns, ok, P);
-            Nsb[tid] = ok ? ns : 0;
-            Pp[tid] = P;
-            Ep[tid] = e;
-            Lp[tid] = L;
-        }
-        __syncthreads();
-        const int ntiles = (nc + bpt - 1) / bpt;
-        load_tile(0, min(bpt, nc));
-        store_tile(0);
-        __syncthreads();
-        for (int t = 0; t < ntiles; ++t) {
-            const int buf = t & 1, c0 = t * bpt, nt = min(bpt, nc - c0);
-            if (t + 1 < ntiles) load_tile(c0 + bpt, min(bpt, nc - c0 - bpt));
-            doublex4 p1 = {0.0, 0.0, 0.0, 0.0}, p2 = {0.0, 0.0, 0.0, 0.0}, p3 = {0.0, 0.0, 0.0, 0.0};
-            const float2 *ecol = Es[buf] + (lane & 15) * kEs + (lane >> 4);
+    float2 ha[KQ + (KQ & 1)], hb[KQ + (KQ & 1)];
+    load_h(tile0, hb);
+    bool resident = false;                                   // both column tiles are in LDS
+    int nc = 0, e1 = 0, e2 = 0;
+    // blocks [0, e1) of the chunk have Ns = 1, [e1, e2) Ns = 2, the rest Ns = 3; a tile takes the
+    // next blocks that fill COLS columns
+    auto tile_at = [&](int c) {
+        Tile t;
+        t.t1 = min(COLS, max(e1 - c, 0));
+        t.t2 = c + t.t1 < e1 ? 0 : min((COLS - t.t1) / 2, max(e2 - c - t.t1, 0));
+        t.t3 = c + t.t1 + t.t2 < e2 ? 0 : min((COLS - t.t1 - 2 * t.t2) / 3,
+                                              max(nc - c - t.t1 - t.t2, 0));
+        return t;
+    };
+    for (int dt = 0; dt < nd; ++dt) {
+        const int d0 = (tile0 + dt) * kRows;
 #pragma unroll
-            for (int q = 0; q < kKq; ++q) {
-                if (q < KQ) {                                // uniform
-                    const float2 e = ecol[4 * q];
-                    const double a = ha[q].x, b = ha[q].y, c = e.x, d = e.y;
-                    p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, c, p1, 0, 0, 0);
-                    p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(b, -d, p2, 0, 0, 0);
-                    p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a + b, c - d, p3, 0, 0, 0);
-                }
-            }
-            const doublex4 gre = p1 - p2, gim = p3 - p1 - p2;
-            // FP64 result layout: element e of lane l is row l / 16 + 4 e, column l % 16
+        for (int q = 0; q < KQ; ++q) ha[q] = hb[q];
+        if constexpr (LOOP)
+            if (dt + 1 < nd) load_h(tile0 + dt + 1, hb);
+        double hn = 0.0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                Gs[wave][((lane >> 4) + 4 * e) * kCols + (lane & 15)] =
-                    make_double2(gre[e], gim[e]);
-            __syncthreads();
-            // items (direction row i of this wave, block bi): den = |h|^2 - |L^{-1} g|^2
-            for (int it = lane; it < 16 * nt; it += 64) {
-                const int i = it / nt, bi = it - i * nt;
-                const int d = d0 + 16 * wave + i;
-                float *P = Pp[c0 + bi];
-                if (d >= D || P == nullptr) continue;
-                const int ns = Nsb[c0 + bi];
-                const double hh = nrm_s[16 * wave + i];
-                float out = 0.0f;
-                if (ns > 0) {
-                    const double2 *g = &Gs[wave][i * kCols + bi * nsmax];
-                    const double2 *L = Ls[buf][bi];
-                    double2 y0 = make_double2(0.0, 0.0), y1 = y0, y2 = y0;
-                    // y = L^{-1} g, L^{-1} lower triangular by rows (00, 10, 11, 20, 21, 22)
-                    const double2 g0 = g[0];
-                    y0 = make_double2(L[0].x * g0.x, L[0].x * g0.y);
-                    double q2 = y0.x * y0.x + y0.y * y0.y;
-                    if (ns >= 2) {
-                        const double2 g1 = g[1];
-                        y1 = make_double2(L[1].x * g0.x - L[1].y * g0.y + L[2].x * g1.x,
-                                          L[1].x * g0.y + L[1].y * g0.x + L[2].x * g1.y);
-                        q2 += y1.x * y1.x + y1.y * y1.y;
-                    }
-                    if (ns >= 3) {
-                        const double2 g1 = g[1], g2 = g[2];
-                        y2 = make_double2(L[3].x * g0.x - L[3].y * g0.y + L[4].x * g1.x -
-                                              L[4].y * g1.y + L[5].x * g2.x,
-                                          L[3].x * g0.y + L[3].y * g0.x + L[4].x * g1.y +
-                                              L[4].y * g1.x + L[5].x * g2.y);
-                        q2 += y2.x * y2.x + y2.y * y2.y;
-                    }
-                    const double den = fmax(hh - q2, 1.17549435e-38);
-                    out = (float)(hh / den);
+        for (int q = 0; q < KQ; ++q)
+            hn = fma((double)ha[q].x, (double)ha[q].x, fma((double)ha[q].y, (double)ha[q].y, hn));
+        hn += __shfl_xor(hn, 16);
+        hn += __shfl_xor(hn, 32);
+        if (lane < 16) nrm_s[16 * wave + lane] = hn;
+
+        for (int h0 = 0; h0 < nb; h0 += CHUNK) {            // chunks of the blocks' descriptors
+            Tile t = tile_at(0);
+            if (!resident) {
+                nc = min(CHUNK, nb - h0);
+                __syncthreads();                             // the previous chunk is finished
+                int myns = 4;
+                if (tid < nc) {
+                    const float2 *e;
+                    const double2 *L;
+                    float *P;
+                    int ns = 0;
+                    bool ok = false;
+                    blk(h0 + tid, e, L, ns, ok, P);
+                    myns = ns;
+                    Nsb[tid] = ok ? ns : 0;
+                    Pp[tid] = P;
+                    Ep[tid] = e;
+                    Lp[tid] = L;
                 }
-                gstore(P + d, out);
+                e1 = __builtin_amdgcn_readfirstlane(__syncthreads_count(myns <= 1));
+                e2 = __builtin_amdgcn_readfirstlane(__syncthreads_count(myns <= 2));
+                t = tile_at(0);
+                load_tile(0, t);
+                store_tile(0);
+                if (LOOP && nb == nc) {                      // uniform
+                    const int c1 = t.blocks();
+                    const Tile tn = tile_at(c1);
+                    resident = c1 + tn.blocks() == nc;
+                    if (resident && c1 < nc) {
+                        load_tile(c1, tn);
+                        store_tile(1);
+                    }
+                }
+                __syncthreads();
             }
-            // the other parity was last read in the previous tile, before this tile's barrier
-            if (t + 1 < ntiles) store_tile(buf ^ 1);
-            __syncthreads();
+            int c0 = 0;
+            for (int buf = 0; c0 < nc; buf ^= 1) {
+                const int nt = t.blocks(), c1 = c0 + nt;
+                Tile tn = t;
+                if (c1 < nc) {
+                    tn = tile_at(c1);
+                    if (!resident) load_tile(c1, tn);
+                }
+                if constexpr (COLS == 16) {
+                    doublex4 p1 = {0.0, 0.0, 0.0, 0.0}, p2 = p1, p3 = p1;
+                    const float2 *ecol = Es[buf] + (lane & 15) * kEs + kl;
+#pragma unroll
+                    for (int q = 0; q < KQ; ++q) {
+                        const float2 e = ecol[4 * q];
+                        // used a few times: not held in FP64 (twice the registers)
+                        if constexpr (LOOP) asm volatile("" : "+v"(ha[q].x), "+v"(ha[q].y));
+                        const double a = ha[q].x, b = ha[q].y, c = e.x, d = e.y;
+                        p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, c, p1, 0, 0, 0);
+                        p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(b, -d, p2, 0, 0, 0);
+                        p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a + b, c - d, p3, 0, 0, 0);
+                    }
+                    const doublex4 gre = p1 - p2, gim = p3 - p1 - p2;
+                    // FP64 result layout: element e of lane l is row l / 16 + 4 e, column l % 16
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        Gs[wave][(kl + 4 * e) * GS + (lane & 15)] = make_double2(gre[e], gim[e]);
+                } else {
+                    double p1 = 0.0, p2 = 0.0, p3 = 0.0;
+                    const float2 *ecol = Es[buf] + (lane & 3) * kEs + kl;
+#pragma unroll
+                    for (int q = 0; q < KQ; ++q) {
+                        const float2 e = ecol[4 * q];
+                        const double a = ha[q].x, b = ha[q].y, c = e.x, d = e.y;
+                        p1 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, c, p1, 0, 0, 0);
+                        p2 = __builtin_amdgcn_mfma_f64_4x4x4f64(b, -d, p2, 0, 0, 0);
+                        p3 = __builtin_amdgcn_mfma_f64_4x4x4f64(a + b, c - d, p3, 0, 0, 0);
+                    }
+                    // lane l: row 4 (l / 4 mod 4) + l / 16, column l % 4
+                    Gs[wave][(4 * ((lane >> 2) & 3) + kl) * GS + (lane & 3)] =
+                        make_double2(p1 - p2, p3 - p1 - p2);
+                }
+                wave_lds_sync();                             // Gs and nrm_s are this wave's own
+                // items (block bi, direction row i of this wave): den = |h|^2 - |L^{-1} g|^2
+                for (int it = lane; it < 16 * nt; it += 64) {
+                    const int bi = it >> 4, i = it & 15;
+                    const int d = d0 + 16 * wave + i;
+                    float *P = Pp[c0 + bi];
+                    if (d >= D || P == nullptr) continue;
+                    const double hh = nrm_s[16 * wave + i];
+                    float out = 0.0f;
+                    if (Nsb[c0 + bi] > 0) {
+                        const double2 *g = &Gs[wave][i * GS + t.column(bi)];
+                        const int ns = t.ns(bi);
+                        const double2 *L = Ls[buf][bi];
+                        // y = L^{-1} g, L^{-1} lower triangular by rows (00, 10, 11, 20, 21, 22)
+                        const double2 g0 = g[0];
+                        const double2 y0 = make_double2(L[0].x * g0.x, L[0].x * g0.y);
+                        double q2 = y0.x * y0.x + y0.y * y0.y;
+                        if (ns >= 2) {
+                            const double2 g1 = g[1];
+                            const double2 y1 = make_double2(
+                                L[1].x * g0.x - L[1].y * g0.y + L[2].x * g1.x,
+                                L[1].x * g0.y + L[1].y * g0.x + L[2].x * g1.y);
+                            q2 += y1.x * y1.x + y1.y * y1.y;
+                            if (ns >= 3) {
+                                const double2 g2 = g[2];
+                                const double2 y2 = make_double2(
+                                    L[3].x * g0.x - L[3].y * g0.y + L[4].x * g1.x - L[4].y * g1.y +
+                                        L[5].x * g2.x,
+                                    L[3].x * g0.y + L[3].y * g0.x + L[4].x * g1.y + L[4].y * g1.x +
+                                        L[5].x * g2.y);
+                                q2 += y2.x * y2.x + y2.y * y2.y;
+                            }
+                        }
+                        const double den = fmax(hh - q2, 1.17549435e-38);
+                        out = (float)(hh * rcp_refined(den));
+                    }
+                    gstore(P + d, out);
+                }
+                wave_lds_sync();
+                // the other parity was last read in the previous tile, before its barrier
+                if (!resident) {
+                    if (c1 < nc) store_tile(buf ^ 1);
+                    __syncthreads();
+                }
+                c0 = c1;
+                t = tn;
+            }
         }
     }
 }
@@ -224,8 +387,8 @@ __device__ __forceinline__ bool sig_item(int n_items, int n_tiles, int &item, in
     return item < n_items;
 }
 
-template <class Tab>
-__global__ __launch_bounds__(kThreads) void steer_sig_single(
+template <class Tab, int KQ>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void steer_sig_single(
     const typename Tab::W *__restrict__ H, const float2 *__restrict__ Es,
     const double2 *__restrict__ Esl,
     const int32_t *__restrict__ bin_status, int F, int D, int M, int Ns, float *__restrict__ P,
@@ -233,7 +396,7 @@ __global__ __launch_bounds__(kThreads) void steer_sig_single(
 {
     int f, tile;
     if (!sig_item(F, n_tiles, f, tile)) return;
-    sig_tile<Tab>(H + (size_t)f * D * M, D, M, tile * kRows, 1, Ns,
+    sig_tile<Tab, 4, KQ, false>(H + (size_t)f * D * M, D, M, tile, 1, 1,
              [&](int, const float2 *&e, const double2 *&L, int &ns, bool &ok, float *&Pf) {
                  e = Es + (size_t)f * Ns * M;
                  L = Esl + 6 * (size_t)f;
@@ -244,24 +407,23 @@ __global__ __launch_bounds__(kThreads) void steer_sig_single(
 }
 
 // Batched: item = (group, bin), groups[g] = (first, count) into gblocks, the blocks of one
-// steering table; nsmax = the largest Ns of the batch.
+// steering table in ascending order of Ns.
 // (3 waves per SIMD: the next tile's operands in registers would otherwise cost one)
-template <class Tab>
+template <class Tab, int KQ, bool LOOP>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(3))) void steer_sig_batch(
     const BlockDev *__restrict__ blk, const int2 *__restrict__ items, int n_items, int n_tiles,
-    const int2 *__restrict__ groups, const int *__restrict__ gblocks, int nsmax)
+    const int2 *__restrict__ groups, const int *__restrict__ gblocks, int per_wg)
 {
     int ii, tile;
     if (!sig_item(n_items, n_tiles, ii, tile)) return;
     const int2 it = items[ii];
     const int2 gr = groups[it.x];
     const BlockDev &B0 = blk[gblocks[gr.x]];
-    const int d0 = tile * kRows;
-    if (d0 >= B0.D) return;
     const int f = it.y, M = B0.M, D = B0.D;
-    sig_tile<Tab>(static_cast<const typename Tab::W *>(B0.H) + (size_t)f * D * M, D, M, d0, gr.y,
-                  nsmax,
+    const int t0 = tile * per_wg, nd = min(per_wg, (D + kRows - 1) / kRows - t0);
+    if (nd <= 0) return;
+    sig_tile<Tab, 16, KQ, LOOP>(static_cast<const typename Tab::W *>(B0.H) + (size_t)f * D * M, D, M, t0, nd, gr.y,
              [&](int i, const float2 *&e, const double2 *&L, int &ns, bool &ok, float *&Pf) {
                  const BlockDev &B = blk[gblocks[gr.x + i]];
                  e = B.Es + (size_t)f * B.Ns * M;
@@ -272,16 +434,39 @@ __attribute__((amdgpu_waves_per_eu(3))) void steer_sig_batch(
              });
 }
 
-// Calls fn with the table reader of prec.
+// Calls fn with the table reader of prec and the k-steps of a class.
 template <class Fn>
-hipError_t with_table(ssl_prec prec, Fn &&fn)
+hipError_t with_variant(ssl_prec prec, int cls, Fn &&fn)
 {
-    if (prec == SSL_BF16) return fn(TabBF16());
-    if (prec == SSL_FP16) return fn(TabF16());
-    return fn(TabF32());
+    auto table = [&](auto kq) {
+        if (prec == SSL_BF16) return fn(TabBF16(), kq);
+        if (prec == SSL_FP16) return fn(TabF16(), kq);
+        return fn(TabF32(), kq);
+    };
+    switch (cls) {
+    case 16: return table(std::integral_constant<int, 4>());
+    case 32: return table(std::integral_constant<int, 8>());
+    case 48: return table(std::integral_constant<int, 12>());
+    case 60: return table(std::integral_constant<int, 15>());
+    default: return table(std::integral_constant<int, 16>());
+    }
 }
 
 }  // namespace
+
+// Direction tiles of a workgroup, 0 for the kernel without the direction loop.  Where a table's blocks
+// fill two column tiles (32 signal vectors) or fewer on average, a workgroup's setup (a chain of
+// descriptor loads, then the signal vectors) costs more than one direction tile, so it is paid once for
+// several: as few as leave 8 workgroups per CU (two or three launch rounds), eight at most.  Measured
+// with 0 / 1 / 2 / 4 / 8 tiles: 8 and 16 channels, 257 bins, 11 blocks 87 / 91 / 72 / 66 / 62 us; 60
+// channels, 5 blocks 100 / 105 / 99 / 108 / 120 us (too few workgroups from 3 tiles on).  With more
+// blocks the setup is hidden and the rows of one direction tile are kept in FP64 instead (128 blocks:
+// 0.78 ms without the loop, 0.86 ms with it).
+int steer_sig_per_wg(int64_t n_items, int n_tiles, double columns, int cus)
+{
+    if (columns > 32.0) return 0;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(8, n_items * n_tiles / (8 * (int64_t)cus)));
+}
 
 int steer_sig_tiles(int D) { return (D + kRows - 1) / kRows; }
 
@@ -290,10 +475,10 @@ hipError_t launch_steer_sig(const void *H, ssl_prec hprec, const ssl_c64 *Es,
                             const int32_t *bin_status, float *P, hipStream_t st)
 {
     const int nt = steer_sig_tiles(D);
-    return with_table(hprec, [&](auto tab) {
+    return with_variant(hprec, steer_sig_class(M), [&](auto tab, auto kq) {
         typedef decltype(tab) Tab;
-        hipLaunchKernelGGL(steer_sig_single<Tab>, dim3(sig_grid(F, nt)), dim3(kThreads), 0, st,
-                           static_cast<const typename Tab::W *>(H),
+        hipLaunchKernelGGL((steer_sig_single<Tab, kq>), dim3(sig_grid(F, nt)), dim3(kThreads), 0,
+                           st, static_cast<const typename Tab::W *>(H),
                            reinterpret_cast<const float2 *>(Es),
                            reinterpret_cast<const double2 *>(Esl), bin_status, F, D, M, Ns, P, nt);
         return hipGetLastError();
@@ -301,15 +486,20 @@ hipError_t launch_steer_sig(const void *H, ssl_prec hprec, const ssl_c64 *Es,
 }
 
 hipError_t launch_steer_sig_batch(const BlockDev *blk, const int2 *items, int n_items,
-                                  const int2 *groups, const int *gblocks, int max_dtiles,
-                                  int nsmax, ssl_prec hprec, hipStream_t st)
+                                  const int2 *groups, const int *gblocks, int cls, int max_dtiles,
+                                  int per_wg, ssl_prec hprec, hipStream_t st)
 {
     if (n_items <= 0) return hipSuccess;
-    return with_table(hprec, [&](auto tab) {
+    const int per = per_wg > 0 ? per_wg : 1, nt = (max_dtiles + per - 1) / per;
+    return with_variant(hprec, cls, [&](auto tab, auto kq) {
         typedef decltype(tab) Tab;
-        hipLaunchKernelGGL(steer_sig_batch<Tab>, dim3(sig_grid(n_items, max_dtiles)),
-                           dim3(kThreads), 0, st, blk, items, n_items, max_dtiles, groups,
-                           gblocks, nsmax);
+        const dim3 grid(sig_grid(n_items, nt)), block(kThreads);
+        if (per_wg > 0)
+            hipLaunchKernelGGL((steer_sig_batch<Tab, kq, true>), grid, block, 0, st, blk, items,
+                               n_items, nt, groups, gblocks, per);
+        else
+            hipLaunchKernelGGL((steer_sig_batch<Tab, kq, false>), grid, block, 0, st, blk, items,
+                               n_items, nt, groups, gblocks, per);
         return hipGetLastError();
     });
 }
