@@ -315,6 +315,9 @@ ssl_status ssl_sliding_corr(ssl_sliding s, ssl_c128 *R, void *stream);
  * re-anchors the singular vectors (rounding in U = U0 V accumulates over warm solves).  Either
  * way the sorted singular vectors are kept for the next call.  Needs at least T pushed frames
  * (SSL_ERR_STATE).
+ * Where ssl_localize stops at the signal subspace (p = 2, Ns <= 3, no GEVD, the default modes of
+ * ssl_ctx_set_svd, ssl_ctx_set_stop and ssl_ctx_set_projection), a call with conv NULL does the same:
+ * faster than either solve, warm or not; it neither reads nor changes the kept singular vectors.
  * conv: [F][3] int32 or NULL (sweeps, rotations, rank as in ssl_gsvd; M for a warm solve).
  * Uses the context's workspace; calls on one ctx must be ordered on one stream. */
 ssl_status ssl_sliding_localize(ssl_sliding s, ssl_noise K, const void *H, ssl_prec prec,
@@ -404,7 +407,8 @@ int ssl_ctx_get_svd(ssl_ctx ctx);
  *   SSL_STOP_LOCALIZE    (default) also ssl_localize and ssl_localize_noalloc with p = 2;
  *   SSL_STOP_ALSO_GSVD   also ssl_gsvd calls that pass sigma = NULL (their E_n is then a basis of
  *                        the noise subspace).
- * ssl_sliding_localize keeps the full solve (its singular vectors seed warm starts).  Results
+ * ssl_sliding_localize keeps the full solve where conv is asked for (its singular vectors seed warm
+ * starts) and follows ssl_localize otherwise.  Results
  * agree with the full solve's within the parity bounds (rounding differs); batched and one-block
  * results are bit-identical when both run the same solve (every mode but SSL_STOP_BATCH).
  * Changing the mode drops captured batch graphs' reuse. */
@@ -430,11 +434,12 @@ int ssl_ctx_get_stop(ssl_ctx ctx);
  * that the iteration cannot decide.
  *   SSL_PROJ_SIGNAL   (default) this form wherever it applies: p = 2, the Jacobi backend, GSVD or
  *                     SEVD (not GEVD, whose noise vectors are not orthonormal), 1 <= Ns <= 3, any
- *                     table precision, in ssl_localize, ssl_localize_noalloc and
- *                     ssl_localize_batch (per block: a batch may mix blocks of both forms);
+ *                     table precision, in ssl_localize, ssl_localize_noalloc, ssl_localize_batch
+ *                     (per block: a batch may mix blocks of both forms) and, without conv and under
+ *                     a stop mode as above, ssl_sliding_localize;
  *   SSL_PROJ_NOISE    always the noise-vector projection H^H E_n (MFMA at the table's
  *                     precision), as ssl_music_spectrum computes it.
- * p = 1, ssl_sliding_localize and ssl_music_spectrum always use the noise-vector projection.  The
+ * p = 1 and ssl_music_spectrum always use the noise-vector projection.  The
  * two forms agree within the parity bounds (rounding differs). */
 typedef enum { SSL_PROJ_NOISE = 0, SSL_PROJ_SIGNAL = 1 } ssl_projection;
 ssl_status ssl_ctx_set_projection(ssl_ctx ctx, ssl_projection mode);

@@ -305,13 +305,13 @@ LocalizeWs localize_ws(int F, int M, int Ns, int D)
     return L;
 }
 
-// The five launches of one block (eq.2-6 and the peak search) on workspace w laid out as L and
-// bin-sum partials `part`.  With `may_time` false no timing event is ever created or recorded.
-ssl_status localize_enqueue(ssl_ctx ctx, bool may_time, char *w, const LocalizeWs &L, float *part,
-                            const ssl_c64 *X, int F, int T, int M, int64_t strideF,
-                            int64_t strideT, ssl_noise K, const void *H, ssl_prec prec, int n_az,
-                            int n_el, int Ns, int p, int32_t *peaks, float *peak_val, float *Pbar,
-                            int32_t *bin_status, hipStream_t st)
+// The launches behind one block's R (at the start of workspace w, laid out as L): eq.4-6 and the peak
+// search, with bin-sum partials `part`.  With `may_time` false no timing event is ever created or
+// recorded.
+ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const LocalizeWs &L, float *part,
+                                 int F, int M, ssl_noise K, const void *H, ssl_prec prec, int n_az,
+                                 int n_el, int Ns, int p, int32_t *peaks, float *peak_val, float *Pbar,
+                                 int32_t *bin_status, hipStream_t st)
 {
     const int D = n_az * n_el;
     ssl_c64 *R = reinterpret_cast<ssl_c64 *>(w);
@@ -324,10 +324,7 @@ ssl_status localize_enqueue(ssl_ctx ctx, bool may_time, char *w, const LocalizeW
     auto run = [&](int id, auto &&launch) {
         return may_time ? timed(ctx, id, st, launch) : launch();
     };
-    hipError_t e = run(SSL_K_CORR, [&] {
-        return launch_corr(X, F, T, M, strideF, strideT, 1.0 / T, 0, prec, R, st);
-    });
-    if (e != hipSuccess) return hip_fail(e, "corr launch");
+    hipError_t e = hipSuccess;
     const bool gevd = use_gevd(ctx, K);
     const bool sig = use_sig(ctx, prec, p, Ns, gevd);
     const bool iter = use_iteration(ctx, M, sig, false);
@@ -373,6 +370,22 @@ ssl_status localize_enqueue(ssl_ctx ctx, bool may_time, char *w, const LocalizeW
         return launch_binsum_peaks(P, F, D, Pb, part, n_az, n_el, Ns, peaks, peak_val, st);
     });
     return e == hipSuccess ? SSL_OK : hip_fail(e, "bin-sum launch");
+}
+
+// One block from its frames: eq.2, then the above.
+ssl_status localize_enqueue(ssl_ctx ctx, bool may_time, char *w, const LocalizeWs &L, float *part,
+                            const ssl_c64 *X, int F, int T, int M, int64_t strideF,
+                            int64_t strideT, ssl_noise K, const void *H, ssl_prec prec, int n_az,
+                            int n_el, int Ns, int p, int32_t *peaks, float *peak_val, float *Pbar,
+                            int32_t *bin_status, hipStream_t st)
+{
+    auto corr = [&] {
+        return launch_corr(X, F, T, M, strideF, strideT, 1.0 / T, 0, prec, w, st);
+    };
+    const hipError_t e = may_time ? timed(ctx, SSL_K_CORR, st, corr) : corr();
+    if (e != hipSuccess) return hip_fail(e, "corr launch");
+    return localize_corr_enqueue(ctx, may_time, w, L, part, F, M, K, H, prec, n_az, n_el, Ns, p, peaks,
+                                 peak_val, Pbar, bin_status, st);
 }
 
 // Fixed device scratch of ssl_localize_noalloc.  Every device the library runs on holds its own
@@ -1052,6 +1065,14 @@ ssl_status ssl_sliding_localize(ssl_sliding s, ssl_noise K, const void *H, ssl_p
     });
     if (e != hipSuccess) return hip_fail(e, "sliding scale launch");
     const bool gevd = use_gevd(ctx, K);
+    // The singular vectors seed a later warm start, and conv reports the solve that finds them.  With
+    // conv NULL the window takes the path of ssl_localize, which needs the signal subspace only and is
+    // faster than a warm start: 60 channels, 257 bins, 1368 directions, windows 10 frames apart with
+    // their pushes 0.195 ms each, 0.62 ms with the whole SVD and the noise vectors; a warm start one
+    // frame on takes 1.5 ms.
+    if (!conv && use_sig(ctx, prec, p, Ns, gevd) && sub_full_for(ctx, p, false) >= 0)
+        return localize_corr_enqueue(ctx, true, w, L, ctx->binsum_part, F, M, K, H, prec, n_az, n_el, Ns,
+                                     p, peaks, peak_val, Pbar, bin_status, st);
     if (gevd) {
         e = timed(ctx, SSL_K_WHITEN, st,
                   [&] { return launch_gevd_whiten(K->Kisq, R, A, F, M, st); });
