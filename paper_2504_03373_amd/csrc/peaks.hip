@@ -10,6 +10,11 @@
 // of its 8 neighbours -- azimuth circular, elevation clamped -- where "beats" means a larger value,
 // or an equal value and a lower flat index.  Maxima are ranked by the same relation; the first
 // Ns are returned, -1 / 0 beyond the number found.  Non-finite values never take part.
+//
+// The second launch is one workgroup's latency: the partials come from other XCDs' L2s, so that those
+// of two directions a thread are loaded at once, and a peak costs one barrier (shuffles within a
+// wave, one LDS exchange between the waves).  257 bins, 1368 directions, 2 peaks: 7.5 us; 11.6 us with loads
+// in groups of 8, early exits from the neighbour tests and a barrier per halving of the maximum.
 #include "ssl_internal.h"
 
 namespace {
@@ -17,82 +22,79 @@ namespace {
 constexpr int kThreads = 256;         // partial sums
 constexpr int kFinal = 1024;          // final sum + peak search, one workgroup per block
 constexpr int kLdsPbar = 8192;        // Pbar staged in LDS when D <= this
+constexpr int kPart = 16;             // chunk partials of a direction in flight
 
-__device__ __forceinline__ bool beats(float va, int a, float vb, int b)
+// "beats" as one comparison: value, then lower index; 0 for a value that takes no part (-0 counts
+// as +0, as in a comparison of floats).
+__device__ __forceinline__ unsigned long long rank_key(float v, int d)
 {
-    return va > vb || (va == vb && a < b);
+    const unsigned int b = __float_as_uint(v + 0.0f);
+    const unsigned int u = b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
+    return isfinite(v) ? ((unsigned long long)u << 32) | ~(unsigned int)d : 0ull;
 }
 
-__device__ bool is_local_max(const float *pb, int n_el, int n_az, int d)
+// The key of direction d if it is a local maximum, else 0.  All neighbours are read at once: in LDS
+// the reads cost less than the branches that would leave early.
+__device__ __forceinline__ unsigned long long peak_key(const float *pb, int n_el, int n_az, int d)
 {
-    const float v = pb[d];
-    if (!isfinite(v)) return false;
     const int el = d / n_az, az = d - el * n_az;
+    const int left = az == 0 ? n_az - 1 : az - 1, right = az == n_az - 1 ? 0 : az + 1;
+    const unsigned long long own = rank_key(pb[d], d);
+    unsigned long long top = 0ull;
+#pragma unroll
     for (int de = -1; de <= 1; ++de) {
-        const int e = el + de;
-        if (e < 0 || e >= n_el) continue;
+        const int e = min(max(el + de, 0), n_el - 1);        // clamped: the own row again
+#pragma unroll
         for (int da = -1; da <= 1; ++da) {
-            if (de == 0 && da == 0) continue;
-            int a = az + da;
-            a = (a < 0) ? a + n_az : (a >= n_az ? a - n_az : a);
-            const int nb = e * n_az + a;
-            if (nb == d) continue;
-            const float w = pb[nb];
-            if (!isfinite(w)) continue;
-            if (!beats(v, d, w, nb)) return false;
+            const int nb = e * n_az + (da < 0 ? left : da > 0 ? right : az);
+            const unsigned long long k = rank_key(pb[nb], nb);
+            top = k > top ? k : top;                         // the direction itself included
         }
     }
-    return true;
+    return top == own ? own : 0ull;
 }
 
-// Whole-workgroup peak search over pb[0..D) (LDS or global).  cand is an LDS flag array of
-// size >= D when D <= kLdsPbar, otherwise candidates are re-tested on the fly.
+// Whole-workgroup peak search over pb[0..D) (LDS or global).  cand is an LDS flag array of size >= D
+// when D <= kLdsPbar; otherwise the maxima are found again for each peak.  The key maximum goes over the
+// lanes of a wave by shuffles and over the waves through LDS.
 __device__ void search_peaks(const float *pb, int D, int n_az, int n_el, int Ns,
                              int32_t *__restrict__ peaks, float *__restrict__ peak_val,
-                             unsigned char *cand, float *red_v, int *red_i, int *chosen)
+                             unsigned char *cand, unsigned long long *red)
 {
-    const int tid = threadIdx.x;
-    const bool use_cand = D <= kLdsPbar;
-    if (use_cand) {
-        for (int d = tid; d < D; d += kFinal) cand[d] = is_local_max(pb, n_el, n_az, d) ? 1 : 0;
-    }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool keep = D <= kLdsPbar;
+    unsigned long long below = ~0ull;                        // peaks so far have larger keys
     for (int k = 0; k < Ns; ++k) {
-        // each thread: best remaining candidate among its directions
-        float bv = 0.f;
-        int bi = -1;
-        for (int d = tid; d < D; d += kFinal) {
-            bool c = use_cand ? (cand[d] != 0) : is_local_max(pb, n_el, n_az, d);
-            if (!c) continue;
-            bool taken = false;
-            for (int j = 0; j < k; ++j) taken |= (chosen[j] == d);
-            if (taken) continue;
-            const float v = pb[d];
-            if (bi < 0 || beats(v, d, bv, bi)) {
-                bv = v;
-                bi = d;
+        unsigned long long best = 0ull;
+        for (int d = tid; d < D; d += kFinal) {              // a thread's own directions each time
+            unsigned long long v;
+            if (keep && k > 0) {
+                v = cand[d] ? rank_key(pb[d], d) : 0ull;
+            } else {
+                v = peak_key(pb, n_el, n_az, d);
+                if (keep) cand[d] = v != 0ull;
             }
+            if (v < below && v > best) best = v;
         }
-        red_v[tid] = bv;
-        red_i[tid] = bi;
+#pragma unroll
+        for (int s = 32; s > 0; s >>= 1) {
+            const unsigned long long o = __shfl_xor(best, s);
+            best = o > best ? o : best;
+        }
+        if (lane == 0) red[(k & 1) * (kFinal / 64) + wave] = best;
         __syncthreads();
-        for (int s = kFinal / 2; s > 0; s >>= 1) {
-            if (tid < s) {
-                const int oi = red_i[tid + s];
-                const float ov = red_v[tid + s];
-                if (oi >= 0 && (red_i[tid] < 0 || beats(ov, oi, red_v[tid], red_i[tid]))) {
-                    red_v[tid] = ov;
-                    red_i[tid] = oi;
-                }
-            }
-            __syncthreads();
+        best = red[(k & 1) * (kFinal / 64) + (lane & (kFinal / 64 - 1))];
+#pragma unroll
+        for (int s = kFinal / 128; s > 0; s >>= 1) {
+            const unsigned long long o = __shfl_xor(best, s);
+            best = o > best ? o : best;
         }
+        below = best;                                        // 0: none left, nor for later peaks
         if (tid == 0) {
-            chosen[k] = red_i[0];
-            peaks[k] = red_i[0];
-            peak_val[k] = red_i[0] >= 0 ? red_v[0] : 0.0f;
+            const int d = best != 0ull ? (int)~(unsigned int)best : -1;
+            peaks[k] = d;
+            peak_val[k] = d >= 0 ? pb[d] : 0.0f;
         }
-        __syncthreads();
     }
 }
 
@@ -124,29 +126,46 @@ __device__ __forceinline__ void binsum_final_body(const float *__restrict__ part
 {
     __shared__ float pb_s[kLdsPbar];
     __shared__ unsigned char cand[kLdsPbar];
-    __shared__ float red_v[kFinal];
-    __shared__ int red_i[kFinal];
-    __shared__ int chosen[SSL_MAX_M];
+    __shared__ unsigned long long red[2 * kFinal / 64];
     const int tid = threadIdx.x;
     const bool lds = D <= kLdsPbar;
-    for (int e = tid; e < D; e += kFinal) {
-        float s = 0.f;
-        int c = 0;
-        for (; c + 8 <= nch; c += 8) {
-            float v[8];
+    // a uniform row and a 32-bit byte offset (D <= 2^24): no address registers per load
+    auto at = [](const float *row, unsigned int x) {
+        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + 4u * x);
+    };
+    // two directions a thread, kPart partials of both in flight (absent ones add an exact 0)
+#pragma unroll 1
+    for (unsigned int e = tid; e < (unsigned int)D; e += 2 * kFinal) {
+        const unsigned int e1 = min(e + kFinal, (unsigned int)D - 1);  // in range; dropped below if not ours
+        float s = 0.f, s1 = 0.f;
+#pragma unroll 1
+        for (int c0 = 0; c0 < nch; c0 += kPart) {
+            float v[kPart], v1[kPart];
+            const float *row = part + (size_t)c0 * D;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = part[(size_t)(c + i) * D + e];
+            for (int i = 0; i < kPart; ++i, row += D) {
+                v[i] = v1[i] = 0.0f;
+                if (c0 + i < nch) {                          // uniform
+                    v[i] = gload(at(row, e));
+                    v1[i] = gload(at(row, e1));
+                }
+            }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s += v[i];
+            for (int i = 0; i < kPart; ++i) {
+                s += v[i];
+                s1 += v1[i];
+            }
         }
-        for (; c < nch; ++c) s += part[(size_t)c * D + e];
-        Pbar[e] = s;
+        gstore(Pbar + e, s);
         if (lds) pb_s[e] = s;
+        if (e + kFinal < D) {
+            gstore(Pbar + e1, s1);
+            if (lds) pb_s[e1] = s1;
+        }
     }
     __syncthreads();
     if (peaks != nullptr)
-        search_peaks(lds ? pb_s : Pbar, D, n_az, n_el, Ns, peaks, peak_val, cand, red_v, red_i,
-                     chosen);
+        search_peaks(lds ? pb_s : Pbar, D, n_az, n_el, Ns, peaks, peak_val, cand, red);
 }
 
 __global__ __launch_bounds__(kThreads) void binsum_part(const float *__restrict__ P, int F, int D,
@@ -189,15 +208,12 @@ __global__ __launch_bounds__(kFinal) void peaks_only(const float *__restrict__ P
 {
     __shared__ float pb_s[kLdsPbar];
     __shared__ unsigned char cand[kLdsPbar];
-    __shared__ float red_v[kFinal];
-    __shared__ int red_i[kFinal];
-    __shared__ int chosen[SSL_MAX_M];
+    __shared__ unsigned long long red[2 * kFinal / 64];
     const bool lds = D <= kLdsPbar;
     if (lds)
         for (int e = threadIdx.x; e < D; e += kFinal) pb_s[e] = Pbar[e];
     __syncthreads();
-    search_peaks(lds ? pb_s : Pbar, D, n_az, n_el, Ns, peaks, peak_val, cand, red_v, red_i,
-                 chosen);
+    search_peaks(lds ? pb_s : Pbar, D, n_az, n_el, Ns, peaks, peak_val, cand, red);
 }
 
 }  // namespace
