@@ -428,10 +428,10 @@ int ssl_ctx_get_stop(ssl_ctx ctx);
  * widened exactly; FP64 matrix cores), with the exact projector E_s (E_s^H E_s)^{-1} E_s^H onto
  * their span (the Jacobi solve returns the inverse Cholesky factor of their FP64 Gram matrix):
  * den = |h|^2 - |L^{-1} E_s^H h|^2, P = |h|^2 / max(den, FLT_MIN).  The Jacobi solve then forms
- * only the signal vectors; with more than 16 channels (and a mode of ssl_ctx_set_stop that lets the
- * solve stop at the subspace) they come from block subspace iteration on K^{-1} R instead, in FP64
- * and converged to the FP32 roundoff of the weakest signal value, the Jacobi solve taking only the bins
- * that the iteration cannot decide.
+ * only the signal vectors; under a mode of ssl_ctx_set_stop that lets the solve stop at the subspace
+ * they come from block subspace iteration on K^{-1} R instead, in FP64 and converged to the FP32
+ * roundoff of the weakest signal value, the Jacobi solve taking only the bins that the iteration cannot
+ * decide.
  *   SSL_PROJ_SIGNAL   (default) this form wherever it applies: p = 2, the Jacobi backend, GSVD or
  *                     SEVD (not GEVD, whose noise vectors are not orthonormal), 1 <= Ns <= 3, any
  *                     table precision, in ssl_localize, ssl_localize_noalloc, ssl_localize_batch

@@ -173,11 +173,11 @@ int sub_full_for(ssl_ctx ctx, int p, bool batched)
     return p == 2 && ctx->sub_stop >= need ? kSubFullSweeps : -1;
 }
 // Whether a block projected through the signal subspace gets it by block subspace iteration
-// (subspace.hip) instead of the Jacobi solve: more than 16 channels, and the solve may stop at the
-// subspace (the iteration knows no other singular vectors).
-bool use_iteration(ssl_ctx ctx, int M, bool sig, bool batched)
+// (subspace.hip) instead of the Jacobi solve: where the solve may stop at the subspace (the iteration
+// knows no other singular vectors).
+bool use_iteration(ssl_ctx ctx, bool sig, bool batched)
 {
-    return sig && subspace_class(M) != 0 && sub_full_for(ctx, 2, batched) >= 0;
+    return sig && sub_full_for(ctx, 2, batched) >= 0;
 }
 int st_waves(ssl_ctx ctx, int M, int Ns, ssl_prec prec)
 {
@@ -327,7 +327,7 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
     hipError_t e = hipSuccess;
     const bool gevd = use_gevd(ctx, K);
     const bool sig = use_sig(ctx, prec, p, Ns, gevd);
-    const bool iter = use_iteration(ctx, M, sig, false);
+    const bool iter = use_iteration(ctx, sig, false);
     if (gevd) {
         e = run(SSL_K_WHITEN, [&] { return launch_gevd_whiten(K->Kisq, R, A, F, M, st); });
         if (e != hipSuccess) return hip_fail(e, "GEVD whitening launch");
@@ -1712,7 +1712,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         }
         key.push_back(d.K ? (use_gevd(ctx, d.K) ? 2 : 1) : 0);
         sigb[b] = use_sig(ctx, prec, p, d.Ns, use_gevd(ctx, d.K)) ? 1 : 0;
-        iterb[b] = use_iteration(ctx, d.M, sigb[b], true) ? 1 : 0;
+        iterb[b] = use_iteration(ctx, sigb[b], true) ? 1 : 0;
         key.push_back(sigb[b]);
         const size_t F = d.F, M = d.M, D = (size_t)d.n_az * d.n_el, Nn = d.M - d.Ns;
         const size_t nch = (F + SSL_BINSUM_CHUNK - 1) / SSL_BINSUM_CHUNK;
@@ -1882,8 +1882,8 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         }
     }
     {
-        // Jacobi items by class, then those of the subspace iteration by its classes: 32 goes with
-        // Jacobi class 32 and 48, 60, 64 with 64, each a contiguous run of items
+        // Jacobi items by class, then those of the subspace iteration by its classes, which are finer:
+        // those of one Jacobi class are a contiguous run of items
         std::vector<Seg> segs;
         build_list(c_jac, Fs, hl + 2 * n_items, segs);
         for (Seg &sg : segs) {
@@ -1893,7 +1893,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             }
             sg.cls -= kIterClass;
             plan.iter.push_back(sg);
-            const int jc = sg.cls == 32 ? 32 : 64;
+            const int jc = jacobi_class(sg.cls);
             if (plan.pending.empty() || plan.pending.back().cls != jc)
                 plan.pending.push_back(Seg{jc, sg.start, 0, 0});
             plan.pending.back().count += sg.count;
@@ -1949,8 +1949,8 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             sg.extra = std::min(sg.count, ctx->cu_count * jacobi_persistent_wg_per_cu(
                                               sg.cls, ctx->jac_lanes[jacobi_class_index(sg.cls)]));
     for (Seg &sg : plan.steer) {
-        sg.waves = ctx->steer_waves[steer_class_index(sg.cls)][prec];
-        const int rows = steer_rows_per_block(sg.waves);
+        if (!sg.sig) sg.waves = ctx->steer_waves[steer_class_index(sg.cls)][prec];
+        const int rows = sg.sig ? 1 : steer_rows_per_block(sg.waves);
         int dt = 0;
         for (int b = 0; b < nblocks; ++b)
             if (c_st[b] == sg.cls && sigb[b] == (sg.sig ? 1 : 0))

@@ -155,10 +155,9 @@ __device__ __forceinline__ void gstore(T *p, T v)
 // same kernel variant whichever entry point schedules it.
 inline int corr_class(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : M <= 48 ? 48 : 64; }
 inline int whiten_class(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
-// M <= 16 stays with the Jacobi solve (0 here)
 inline int subspace_class(int M)
 {
-    return M <= 16 ? 0 : M <= 32 ? 32 : M <= 48 ? 48 : M <= 60 ? 60 : 64;
+    return M <= 8 ? 8 : M <= 16 ? 16 : M <= 32 ? 32 : M <= 48 ? 48 : M <= 60 ? 60 : 64;
 }
 inline int jacobi_class(int M) { return M <= 8 ? 8 : M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 // of the signal-subspace projection (k-steps of its products)
@@ -260,7 +259,7 @@ hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int N
                          int32_t *bin_status, int32_t *conv, hipStream_t st,
                          ssl_c64 *U = nullptr, int sub_full = -1, ssl_c64 *Es = nullptr,
                          ssl_c128 *Esl = nullptr, bool pending = false);
-// Signal vectors by block subspace iteration (subspace.hip, subspace_class(M) != 0, Ns <= 3): Es,
+// Signal vectors by block subspace iteration (subspace.hip, Ns <= 3): Es,
 // Esl and status SSL_BIN_OK, or status SSL_BIN_PENDING and A = K^{-1} R (A itself where Kinv is
 // null: R) for the Jacobi solve that has to follow -- launch_jacobi with pending, or
 // launch_jacobi_pending over the same items (whose blocks all have Es and p = 2).

@@ -39,7 +39,10 @@
 // complex element per lane, wave 1 (orthonormalisation) beside wave 0 (test).
 //   Measured, 128 60-channel blocks per launch (32896 bins): 2.5 ms, where the whitening launch (0.98 ms)
 // and the Jacobi launch (6.8 ms) stood before; one block (257 bins): 93 us, 18.7 + 505 us before.
-// M <= 16 stays with the Jacobi solve, whose matrix is then no larger than the block's.
+//   Up to 16 channels one wave does all of a bin, tests before it orthonormalises, and with up to 8
+// starts from the whole space, so that one Jacobi solve of the 8 x 8 matrix and one application decide.
+// 8 channels, 257 bins: 14.6 us; the whitening and Jacobi launches took 2.5 + 23.5 us.  24 blocks each of 8 and
+// of 16 channels with 257 and 513 bins: 0.11 and 0.135 ms (Jacobi: 0.175 and 0.25 ms, whitening 0.017).
 #include "signal_out.h"
 
 namespace {
@@ -54,6 +57,10 @@ constexpr int kMaxSweeps = 12;       // Jacobi sweeps over the 8 x 8 Gram matrix
 constexpr double kCouple = 1e-9;     // (S-rest coupling / gap)^2 that the first-order test copes with
 constexpr int kAccel = 3;            // first step followed by a Chebyshev filter when not done
 constexpr int kDegree = 3;           // its degree
+// The filter scales direction 1 against S by up to (theta_1 / theta_S)^3, and V departs from orthonormality
+// by 2^-53 of that, which the test sees times theta_1: beyond this ratio a filtered block is followed
+// by a plain step before it is filtered again (fourth root of 2^-24 2^53)
+constexpr double kWide = 152.0;
 constexpr double kTol = 5.9604644775390625e-08;      // 2^-24
 constexpr double kRange = 1e-6;      // theta_Ns / theta_1 below this: left to the Jacobi solve
 constexpr int kExpMin = -80, kExpMax = 100;   // max |A| outside 2^.. this: left to the Jacobi solve
@@ -342,11 +349,16 @@ __device__ __forceinline__ void prepare_test(double2 t, int Ns, int lane, Sh &sh
     }
     put_real(sh.BY, i, j, q);
     put_real(sh.BV, i, j, v);
-    // Gershgorin: theta_{Ns+1} <= max of the absolute row sums over the other indices; theta_Ns >=
-    // the smallest diagonal less the row's off-diagonal sum over S (Ns = 2: the exact value)
+    // Gershgorin: theta_{Ns+1} <= max of the absolute row sums over the other indices; theta_Ns >= the
+    // smallest diagonal less its scaled row's off-diagonal sum over S (Ns = 2: the exact value)
     const double at = fabs(t.x) + fabs(t.y);
     double rs = i >= Ns && j >= Ns ? at : 0.0;
-    double lo = i < Ns && j < Ns && i != j ? at : 0.0;
+    double lo = 0.0;
+    if (Ns > 2 && i < Ns && j < Ns && i != j) {
+        // rows scaled by the diagonal's roots: a row far below the first's keeps its bound
+        const double wi = rsqrt64(fmax(di, 1e-200)), wj = rsqrt64(fmax(dj, 1e-200));
+        lo = at * (di * wi * wj);
+    }
     double sm = di;
 #pragma unroll
     for (int o = 1; o < 8; o <<= 1) {
@@ -491,9 +503,22 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
     auto oph32 = [&](int q) { return make_float2(hw[q].x, -hw[q].y); };
 
     double y[4];
-    strip_product32<KQ>(opa32, [&](int q) { return omega(4 * q + kl, cl); }, sgn, y);
     bool solved = false;
     double v[4] = {0.0, 0.0, 0.0, 0.0};                // V on this wave's rows
+    // M <= 8: the block starts as the whole space and only has to be turned to the Ritz vectors
+    constexpr bool whole = 4 * KQ <= kBlk;
+    if constexpr (whole) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = kl + 4 * e == cl && cl < kBlk ? 1.0 : 0.0;
+        store(sh.V, v);
+        __syncthreads();
+        strip_product<KQ>(oph, from(sh.V), sgn, y);
+        store(sh.W, y);
+        __syncthreads();
+        strip_product<KQ>(opa, from(sh.W), sgn, y);
+    } else {
+        strip_product32<KQ>(opa32, [&](int q) { return omega(4 * q + kl, cl); }, sgn, y);
+    }
     // a wave's rows' share of a Gram matrix a^H b, combined to the complex 8 x 8 form
     auto gram = [&](const double (&a)[4], const double (&b)[4], double *out) {
         doublex4 s = {0.0, 0.0, 0.0, 0.0};
@@ -513,67 +538,86 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
         return g;
     };
     bool plain = true;                                 // y = A A^H V (not a filtered block)
-    for (int step = 0;;) {
+    bool fresh = true;                                 // V is not from a filtered block
+    // the test: r = Y q_S - V q_S M on this wave's rows
+    auto residual = [&] {
+        doublex4 zz = {0.0, 0.0, 0.0, 0.0}, x = zz;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 4 * q + kl, o = 16 * k + cl;
+            zz = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.Y[row * kLd + k], sh.BY[o], zz, 0, 0, 0);
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.V[row * kLd + k], sh.BV[o], x, 0, 0, 0);
+        }
+        double n2 = 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double d = zz[e] - x[e];
+            n2 = fma(d, d, n2);
+        }
+        n2 = row_sum(n2);
+        n2 += __shfl_xor(n2, 16);
+        n2 += __shfl_xor(n2, 32);
+        if (lane == 0) sh.rpart[wave] = n2;
+    };
+    auto apart = [&] { return sh.coupled == 0 && sh.thR < sh.thS; };
+    auto passes = [&] {                                // the same in every thread
+        double off = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) off += sh.rpart[w];
+        const double thS = sh.thS, thR = sh.thR;
+        return apart() && thS >= kRange * sh.th1 &&
+               off * (thR * thR) <= (kTol * thS) * (kTol * thS) * (thS * thS);
+    };
+    for (int step = whole ? kFirstTest - 1 : 0;;) {
         const bool test = step >= kFirstTest && plain;
         gram(y, y, sh.part[wave][0]);
         if (test) gram(v, y, sh.part[wave][1]);
-        if (step < kFirstTest) store32(sh.Y, y);
+        if (step < kFirstTest && !whole) store32(sh.Y, y);
         else store(sh.Y, y);                           // own rows only: the operand of Y B, Y BY
         __syncthreads();
-        if (wave == 1) {
+        if (NW == 1 && test) {                         // nobody to orthonormalise beside the test
+            prepare_test(sum_parts(1), Ns, lane, sh);
+            __syncthreads();
+            residual();
+            __syncthreads();
+            if (passes()) {
+                solved = true;
+                break;
+            }
+        }
+        if (wave == (NW > 1 ? 1 : 0)) {
             double2 G = sum_parts(0);
             const int i = lane >> 3, j = lane & 7;
             if (i == j) G.y = 0.0;
             double2 Q = make_double2(i == j ? 1.0 : 0.0, 0.0);
-            if (step >= kFirstTest)
-                ritz(G, Q, Ns, step == kFirstTest ? 1e-2 : kCouple, lane);
+            if (step >= kFirstTest || whole)
+                ritz(G, Q, Ns, step == kFirstTest && !whole ? 1e-2 : kCouple, lane);
             const double2 a = orth_factor(G, Q, lane);
             put_real(sh.B, j, i, conjd(a));
         }
-        if (wave == 0 && test) prepare_test(sum_parts(1), Ns, lane, sh);
+        if (NW > 1 && wave == 0 && test) prepare_test(sum_parts(1), Ns, lane, sh);
         __syncthreads();
-        // V' = Y B and, for the test, z = Y q_S and r = z - V q_S M, on this wave's rows
-        doublex4 vn = {0.0, 0.0, 0.0, 0.0}, zz = vn, x = vn;
+        // V' = Y B and, for the test, r, on this wave's rows
+        doublex4 vn = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int k = 4 * q + kl, o = 16 * k + cl;
-            const double yk = sh.Y[row * kLd + k];
-            vn = __builtin_amdgcn_mfma_f64_16x16x4f64(yk, sh.B[o], vn, 0, 0, 0);
-            if (test) {
-                zz = __builtin_amdgcn_mfma_f64_16x16x4f64(yk, sh.BY[o], zz, 0, 0, 0);
-                x = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.V[row * kLd + k], sh.BV[o], x, 0, 0, 0);
-            }
+            const int k = 4 * q + kl;
+            vn = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.Y[row * kLd + k], sh.B[16 * k + cl], vn, 0, 0, 0);
         }
-        if (test) {
-            double n2 = 0.0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double d = zz[e] - x[e];
-                n2 = fma(d, d, n2);
-            }
-            n2 = row_sum(n2);
-            n2 += __shfl_xor(n2, 16);
-            n2 += __shfl_xor(n2, 32);
-            if (lane == 0) sh.rpart[wave] = n2;
-        }
+        if (NW > 1 && test) residual();
         {
             const double vs[4] = {vn[0], vn[1], vn[2], vn[3]};
             store(sh.V, vs);
         }
         __syncthreads();
-        if (test) {                                    // the same in every thread
-            double off = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) off += sh.rpart[w];
-            const double th1 = sh.th1, thS = sh.thS, thR = sh.thR;
-            const bool apart = sh.coupled == 0 && thR < thS;
-            if (apart && thS >= kRange * th1 &&
-                off * (thR * thR) <= (kTol * thS) * (kTol * thS) * (thS * thS)) {
+        if (test) {
+            if (NW > 1 && passes()) {
                 solved = true;
                 break;
             }
+            const double th1 = sh.th1, thS = sh.thS;
             if (step >= kMaxSteps || !(th1 > 0.0) || ex < kExpMin || ex > kExpMax) break;
-            if (step >= kAccel && apart && sh.thC > kRange * thS) {
+            if (step >= kAccel && apart() && sh.thC > kRange * thS && (fresh || th1 <= kWide * thS)) {
                 // slow bin: the block filtered by the Chebyshev polynomial of A A^H on [0, thC], thC
                 // the smallest Ritz value: W_0 = V, W_1 = (a A A^H - 1) V, W_{k+1} = 2 (a A A^H - 1)
                 // W_k - W_{k-1}, from the V and Y at hand
@@ -606,6 +650,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = sh.V[wr + 4 * e * kLd];
+        fresh = plain;
         plain = true;
         ++step;
         if (step < kFirstTest) {
@@ -700,6 +745,8 @@ template <class Fn>
 hipError_t with_class(int cls, Fn &&fn)
 {
     switch (cls) {
+    case 8: return fn.template operator()<1, 2>();
+    case 16: return fn.template operator()<1, 4>();
     case 32: return fn.template operator()<2, 8>();
     case 48: return fn.template operator()<3, 12>();
     case 60: return fn.template operator()<4, 15>();
