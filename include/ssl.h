@@ -315,7 +315,7 @@ ssl_status ssl_sliding_corr(ssl_sliding s, ssl_c128 *R, void *stream);
  * re-anchors the singular vectors (rounding in U = U0 V accumulates over warm solves).  Either
  * way the sorted singular vectors are kept for the next call.  Needs at least T pushed frames
  * (SSL_ERR_STATE).
- * Where ssl_localize stops at the signal subspace (p = 2, Ns <= 3, no GEVD, the default modes of
+ * Where ssl_localize stops at the signal subspace (p = 2, Ns <= 3, the default modes of
  * ssl_ctx_set_svd, ssl_ctx_set_stop and ssl_ctx_set_projection), a call with conv NULL does the same:
  * faster than either solve, warm or not; it neither reads nor changes the kept singular vectors.
  * conv: [F][3] int32 or NULL (sweeps, rotations, rank as in ssl_gsvd; M for a warm solve).
@@ -432,8 +432,9 @@ int ssl_ctx_get_stop(ssl_ctx ctx);
  * they come from block subspace iteration on K^{-1} R instead, in FP64 and converged to the FP32
  * roundoff of the weakest signal value, the Jacobi solve taking only the bins that the iteration cannot
  * decide.
- *   SSL_PROJ_SIGNAL   (default) this form wherever it applies: p = 2, the Jacobi backend, GSVD or
- *                     SEVD (not GEVD, whose noise vectors are not orthonormal), 1 <= Ns <= 3, any
+ *   SSL_PROJ_SIGNAL   (default) this form wherever it applies: p = 2, the Jacobi backend,
+ *                     1 <= Ns <= 3 (GEVD: with h replaced by K^{-1/2} h in the denominator, for two and
+ *                     three sources and 30..32, 45..48 or 60 channels, where it is faster), any
  *                     table precision, in ssl_localize, ssl_localize_noalloc, ssl_localize_batch
  *                     (per block: a batch may mix blocks of both forms) and, without conv and under
  *                     a stop mode as above, ssl_sliding_localize;

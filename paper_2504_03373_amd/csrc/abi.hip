@@ -155,13 +155,20 @@ hipError_t launch_svd(ssl_ctx ctx, ssl_c64 *A, const int32_t *kst, int F, int M,
                          U, sub_full, Es, Esl);
 }
 // Whether eq.5 is evaluated through the signal subspace (FP64, steer_sig.hip): p = 2, the Jacobi
-// backend, GSVD or SEVD (U unitary), Ns <= 3, any table precision, unless the context asks for
-// the noise-vector projection.
-bool use_sig(ssl_ctx ctx, ssl_prec prec, int p, int Ns, bool gevd)
+// backend, Ns <= 3, any table precision, unless the context asks for the noise-vector projection.
+// GEVD-MUSIC (on K^{-1/2} h): only where that is no slower (to 4%) even when every block of a batch has a
+// noise set of its own and |K^{-1/2} h|^2 serves one block each -- a block's results do not depend on the
+// batch it is in, so the choice cannot -- which takes nearly full tiles of 16 rows (at most one row per
+// tile empty) and the longer Jacobi solves of two and three sources.  257 bins, 1368 directions, 8 blocks
+// of two sources, us with the noise-vector form / with this form on sets of their own / on one set: 17 channels 359
+// / 565 / 214, 32: 610 / 592 / 229, 33: 944 / 1171 / 403, 48: 1527 / 1217 / 437, 56: 1712 / 1767 / 567, 60: 1832 /
+// 1780 / 579, 64 (whose K^{-1/2} leaves LDS for one workgroup per CU): 1877 / 2411 / 713; 60 with one source 1745 / 1839
+// / 650.  One block: 60 channels 423 / 296, 32 channels 202 / 125.
+bool use_sig(ssl_ctx ctx, int M, int p, int Ns, bool gevd)
 {
-    (void)prec;
-    return ctx->proj == SSL_PROJ_SIGNAL && p == 2 && ctx->svd == SSL_SVD_JACOBI && !gevd &&
-           Ns >= 1 && Ns <= 3;
+    const int tiles = (M + 15) / 16;
+    if (gevd && (Ns < 2 || M <= 16 || M > 60 || 16 * tiles - M > tiles)) return false;
+    return ctx->proj == SSL_PROJ_SIGNAL && p == 2 && ctx->svd == SSL_SVD_JACOBI && Ns >= 1 && Ns <= 3;
 }
 
 // Whether a localization path stops the Jacobi solve at the noise subspace (p = 2: eq.5 reads only
@@ -326,7 +333,7 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
     };
     hipError_t e = hipSuccess;
     const bool gevd = use_gevd(ctx, K);
-    const bool sig = use_sig(ctx, prec, p, Ns, gevd);
+    const bool sig = use_sig(ctx, M, p, Ns, gevd);
     const bool iter = use_iteration(ctx, sig, false);
     if (gevd) {
         e = run(SSL_K_WHITEN, [&] { return launch_gevd_whiten(K->Kisq, R, A, F, M, st); });
@@ -343,8 +350,8 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
     ssl_c128 *Esl = sig ? reinterpret_cast<ssl_c128 *>(w + L.off_es() + L.bEs) : nullptr;
     e = run(SSL_K_JACOBI, [&] {
         if (iter) {
-            const hipError_t le = launch_subspace(K ? K->Kinv : nullptr, K ? K->status : nullptr, R,
-                                                  A, F, M, Ns, stt, Es, Esl, st);
+            const hipError_t le = launch_subspace(K && !gevd ? K->Kinv : nullptr, K ? K->status : nullptr,
+                                                  gevd ? A : R, A, F, M, Ns, stt, Es, Esl, st);
             if (le != hipSuccess) return le;
             return launch_jacobi(A, K ? K->status : nullptr, F, M, Ns, SSL_DEFAULT_SWEEPS,
                                  jac_lanes(ctx, M), nullptr, nullptr, stt, nullptr, st, nullptr,
@@ -356,11 +363,14 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
                           sub_full_for(ctx, p, false), Es, Esl);
     });
     if (e != hipSuccess) return hip_fail(e, "jacobi launch");
-    if (gevd) {
+    if (gevd && !sig) {
         e = run(SSL_K_WHITEN, [&] { return launch_gevd_back(K->Kisq, En, F, M, Ns, st); });
         if (e != hipSuccess) return hip_fail(e, "GEVD back-transformation launch");
     }
     e = run(SSL_K_STEER, [&] {
+        if (sig && gevd)
+            return launch_steer_gevd(K->Kisq, H, prec, Es, Esl, F, D, M, Ns, stt, P,
+                                     steer_gevd_per_wg(F, steer_sig_tiles(D), ctx->cu_count), st);
         if (sig)
             return launch_steer_sig(H, prec, Es, Esl, F, D, M, Ns, stt, P, st);
         return launch_steer(H, prec, En, F, D, M, Ns, p, stt, P, st_waves(ctx, M, Ns, prec), st);
@@ -1070,7 +1080,7 @@ ssl_status ssl_sliding_localize(ssl_sliding s, ssl_noise K, const void *H, ssl_p
     // faster than a warm start: 60 channels, 257 bins, 1368 directions, windows 10 frames apart with
     // their pushes 0.195 ms each, 0.62 ms with the whole SVD and the noise vectors; a warm start one
     // frame on takes 1.5 ms.
-    if (!conv && use_sig(ctx, prec, p, Ns, gevd) && sub_full_for(ctx, p, false) >= 0)
+    if (!conv && use_sig(ctx, M, p, Ns, gevd) && sub_full_for(ctx, p, false) >= 0)
         return localize_corr_enqueue(ctx, true, w, L, ctx->binsum_part, F, M, K, H, prec, n_az, n_el, Ns,
                                      p, peaks, peak_val, Pbar, bin_status, st);
     if (gevd) {
@@ -1131,9 +1141,8 @@ struct Seg {
     int cls, start, count, extra;
     int waves = 0;                         // projection: waves per workgroup, or (signal subspace)
                                            // direction tiles per workgroup
-                                           // (steer_sig_per_wg)
     double columns = 0.0;                  // signal vectors per steering table, over its items
-    bool sig = false;                      // projection: through the signal subspace
+    int form = 0;                          // projection: 0 noise vectors, 1 signal subspace, 2 GEVD's
 };
 
 // Launch plan of one batch shape: per kernel, contiguous runs of items sharing a size class.
@@ -1143,7 +1152,8 @@ struct Plan {
     // over the same items, by Jacobi class, for the bins it leaves
     std::vector<Seg> iter, pending;
     int nblocks = 0, n_items = 0, max_dc = 0, max_fc = 0;
-    std::vector<Seg> gevd;                 // (block, bin) items of GEVD-MUSIC blocks, by class
+    std::vector<Seg> gevd;                 // (block, bin) items of GEVD-MUSIC blocks, by class; the
+                                           // first `extra` of a class form noise vectors
 };
 
 // Device tail of the descriptor buffer after the four item lists: steering groups (first, count)
@@ -1302,14 +1312,18 @@ hipError_t enqueue_batch(ssl_ctx ctx, const Plan &P, const BlockDev *blk, const 
         if (e != hipSuccess) return e;
     }
     for (const Seg &s : P.gevd) {
+        if (s.extra == 0) continue;
         e = timed(ctx, SSL_K_WHITEN, st, [&] {
-            return launch_gevd_back_batch(blk, l_gevd + s.start, s.count, s.cls, st);
+            return launch_gevd_back_batch(blk, l_gevd + s.start, s.extra, s.cls, st);
         });
         if (e != hipSuccess) return e;
     }
     for (const Seg &s : P.steer) {
         e = timed(ctx, SSL_K_STEER, st, [&] {
-            if (s.sig)
+            if (s.form == 2)
+                return launch_steer_gevd_batch(blk, l_st + s.start, s.count, ga.groups, ga.gblocks, s.cls,
+                                               s.extra, s.waves, prec, st);
+            if (s.form == 1)
                 return launch_steer_sig_batch(blk, l_st + s.start, s.count, ga.groups, ga.gblocks, s.cls,
                                               s.extra, s.waves, prec, st);
             return launch_steer_batch(blk, l_st + s.start, s.count, ga.groups, ga.gblocks, s.cls,
@@ -1711,7 +1725,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             return s;
         }
         key.push_back(d.K ? (use_gevd(ctx, d.K) ? 2 : 1) : 0);
-        sigb[b] = use_sig(ctx, prec, p, d.Ns, use_gevd(ctx, d.K)) ? 1 : 0;
+        sigb[b] = !use_sig(ctx, d.M, p, d.Ns, use_gevd(ctx, d.K)) ? 0 : use_gevd(ctx, d.K) ? 2 : 1;
         iterb[b] = use_iteration(ctx, sigb[b], true) ? 1 : 0;
         key.push_back(sigb[b]);
         const size_t F = d.F, M = d.M, D = (size_t)d.n_az * d.n_el, Nn = d.M - d.Ns;
@@ -1817,9 +1831,12 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
     for (int cls : {16, 32, 64}) {                    // GEVD products: (block, bin) by class
         Seg sg{cls, 0, 0, 0};
         sg.start = plan.gevd.empty() ? 0 : plan.gevd.back().start + plan.gevd.back().count;
-        for (int b = 0; b < nblocks; ++b)
-            if (hb[b].Kisq && c_wh[b] == cls)
-                for (int f = 0; f < hb[b].F; ++f) hgevd[sg.start + sg.count++] = make_int2(b, f);
+        for (bool sig : {false, true}) {
+            for (int b = 0; b < nblocks; ++b)
+                if (hb[b].Kisq && c_wh[b] == cls && (sigb[b] != 0) == sig)
+                    for (int f = 0; f < hb[b].F; ++f) hgevd[sg.start + sg.count++] = make_int2(b, f);
+            if (!sig) sg.extra = sg.count;
+        }
         if (sg.count) plan.gevd.push_back(sg);
     }
     {
@@ -1905,11 +1922,13 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         int *hgb = reinterpret_cast<int *>(hg + 2 * nblocks);
         std::vector<int> first;                       // first block of each group
         std::vector<std::vector<int>> members;
-        std::map<std::tuple<int, const void *, int, int, int, int>, int> group_of;
+        std::map<std::tuple<int, const void *, int, int, int, int, const void *>, int> group_of;
         for (int b = 0; b < nblocks; ++b) {
             const BlockDev &B = hb[b];
             const auto ins = group_of.emplace(
-                std::make_tuple(c_st[b], B.H, B.F, B.D, B.M, (int)sigb[b]), (int)first.size());
+                std::make_tuple(c_st[b], B.H, B.F, B.D, B.M, (int)sigb[b],
+                                sigb[b] == 2 ? (const void *)B.Kisq : nullptr),
+                (int)first.size());
             const int g = ins.first->second;
             if (ins.second) {
                 first.push_back(b);
@@ -1932,9 +1951,9 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         int2 *out = hl + 3 * n_items;
         int pos = 0;
         for (int c : classes)
-            for (int kind = 0; kind < 2; ++kind) {         // noise-vector, then signal-subspace
+            for (int kind = 0; kind < 3; ++kind) {
                 Seg sg{c, pos, 0, 0};
-                sg.sig = kind == 1;
+                sg.form = kind;
                 for (size_t g = 0; g < members.size(); ++g) {
                     if (c_st[first[g]] != c || sigb[first[g]] != kind) continue;
                     for (int b : members[g]) sg.columns += (double)hb[b].Ns * hb[b].F;
@@ -1949,14 +1968,15 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             sg.extra = std::min(sg.count, ctx->cu_count * jacobi_persistent_wg_per_cu(
                                               sg.cls, ctx->jac_lanes[jacobi_class_index(sg.cls)]));
     for (Seg &sg : plan.steer) {
-        if (!sg.sig) sg.waves = ctx->steer_waves[steer_class_index(sg.cls)][prec];
-        const int rows = sg.sig ? 1 : steer_rows_per_block(sg.waves);
+        if (sg.form == 0) sg.waves = ctx->steer_waves[steer_class_index(sg.cls)][prec];
+        const int rows = sg.form ? 1 : steer_rows_per_block(sg.waves);
         int dt = 0;
         for (int b = 0; b < nblocks; ++b)
-            if (c_st[b] == sg.cls && sigb[b] == (sg.sig ? 1 : 0))
-                dt = std::max(dt, sg.sig ? steer_sig_tiles(hb[b].D) : (hb[b].D + rows - 1) / rows);
+            if (c_st[b] == sg.cls && sigb[b] == sg.form)
+                dt = std::max(dt, sg.form ? steer_sig_tiles(hb[b].D) : (hb[b].D + rows - 1) / rows);
         sg.extra = dt;
-        if (sg.sig) sg.waves = steer_sig_per_wg(sg.count, dt, sg.columns / sg.count, ctx->cu_count);
+        if (sg.form == 1) sg.waves = steer_sig_per_wg(sg.count, dt, sg.columns / sg.count, ctx->cu_count);
+        if (sg.form == 2) sg.waves = steer_gevd_per_wg(sg.count, dt, ctx->cu_count);
     }
 
     e = hipMemcpyAsync(ctx->bdesc_dev, ctx->bdesc_host, desc_bytes + list_bytes,

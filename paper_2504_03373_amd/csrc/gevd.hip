@@ -14,7 +14,7 @@
 //   gevd_whiten  per block: C = W R W on the matrix cores, T = W R kept in LDS in FP64 and
 //                C = W T^H (R and W Hermitian), rounded once to complex64 for the SVD;
 //   gevd_back    per block: E_n <- W E_n on the matrix cores (the SVD's noise vectors mapped to
-//                generalized eigenvectors).
+//                generalized eigenvectors); not where eq.5 goes through the signal vectors of C.
 #include "ssl_internal.h"
 
 namespace {
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kThreads) void noise_isqrt(const double2 *__restric
 }
 
 // The two per-block products on the matrix cores in FP64 (v_mfma_f64_16x16x4f64), as the GSVD
-// whitening: complex products split into real ones over k-steps of 4; NT = MP / 16 waves, wave w
+// whitening: complex products on three real ones (Gauss's trick) over k-steps of 4; NT = MP / 16 waves, wave w
 // owning rows 16 w .. 16 w + 15 of the result and all its column tiles, its A operands (W's rows)
 // in registers.  Padding rows, columns and k-steps (beyond M) are zero on both operands.
 typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -195,23 +195,19 @@ __device__ __forceinline__ void wmul(const double2 (&w)[GvCfg<MP>::KQ], int M, d
     const int KQ = (M + 3) >> 2;
 #pragma unroll
     for (int ct = 0; ct < GvCfg<MP>::NT; ++ct) {
-        ar[ct] = doublex4{0.0, 0.0, 0.0, 0.0};
-        ai[ct] = doublex4{0.0, 0.0, 0.0, 0.0};
-    }
+        if (ct >= nct) continue;                   // uniform
+        doublex4 p1 = {0.0, 0.0, 0.0, 0.0}, p2 = p1, p3 = p1;
 #pragma unroll
-    for (int q = 0; q < GvCfg<MP>::KQ; ++q) {
-        if (q < KQ) {                              // uniform; w[] stays register-indexed
-#pragma unroll
-            for (int ct = 0; ct < GvCfg<MP>::NT; ++ct) {
-                if (ct < nct) {
-                    const double2 b = bop(q, ct);
-                    ar[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].x, b.x, ar[ct], 0, 0, 0);
-                    ar[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].y, -b.y, ar[ct], 0, 0, 0);
-                    ai[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].x, b.y, ai[ct], 0, 0, 0);
-                    ai[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].y, b.x, ai[ct], 0, 0, 0);
-                }
+        for (int q = 0; q < GvCfg<MP>::KQ; ++q) {
+            if (q < KQ) {                          // uniform; w[] stays register-indexed
+                const double2 b = bop(q, ct);
+                p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].x, b.x, p1, 0, 0, 0);
+                p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].y, b.y, p2, 0, 0, 0);
+                p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(w[q].x + w[q].y, b.x + b.y, p3, 0, 0, 0);
             }
         }
+        ar[ct] = p1 - p2;
+        ai[ct] = p3 - p1 - p2;
     }
 }
 

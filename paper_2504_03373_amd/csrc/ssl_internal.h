@@ -195,6 +195,14 @@ int steer_sig_per_wg(int64_t n_items, int n_tiles, double columns, int cus);
 hipError_t launch_steer_sig_batch(const BlockDev *blk, const int2 *items, int n_items,
                                   const int2 *groups, const int *gblocks, int cls, int max_dtiles,
                                   int per_wg, ssl_prec hprec, hipStream_t st);
+// The same for GEVD-MUSIC, on W h (W = K^{-1/2}, Es and Esl of C = W R W).  A group's blocks share W too.
+int steer_gevd_per_wg(int64_t n_items, int n_tiles, int cus);
+hipError_t launch_steer_gevd(const ssl_c128 *W, const void *H, ssl_prec hprec, const ssl_c64 *Es,
+                             const ssl_c128 *Esl, int F, int D, int M, int Ns, const int32_t *bin_status,
+                             float *P, int per_wg, hipStream_t st);
+hipError_t launch_steer_gevd_batch(const BlockDev *blk, const int2 *items, int n_items,
+                                   const int2 *groups, const int *gblocks, int cls, int max_dtiles,
+                                   int per_wg, ssl_prec hprec, hipStream_t st);
 hipError_t launch_steer_batch(const BlockDev *blk, const int2 *items, int n_items,
                               const int2 *groups, const int *gblocks, int cls, int waves,
                               int max_dtiles, ssl_prec hprec, hipStream_t st);

@@ -735,8 +735,9 @@ __attribute__((amdgpu_waves_per_eu(3))) void subspace_batch(
     const BlockDev &B = blk[it.x];
     const int f = it.y, M = B.M, Ns = B.Ns;
     const size_t o = (size_t)f * M * M;
-    subspace_bin<NW, KQ>(B.Kinv ? B.Kinv + o : nullptr, B.kstatus ? B.kstatus[f] : SSL_BIN_OK,
-                         B.R + o, B.A + o, M, Ns, B.conv != nullptr, B.status + f,
+    const bool whiten = B.Kinv && !B.Kisq;             // GEVD: A = C = W R W is there already
+    subspace_bin<NW, KQ>(whiten ? B.Kinv + o : nullptr, B.kstatus ? B.kstatus[f] : SSL_BIN_OK,
+                         (B.Kisq ? B.A : B.R) + o, B.A + o, M, Ns, B.conv != nullptr, B.status + f,
                          B.Es + (size_t)f * Ns * M, B.Esl + 6 * (size_t)f);
 }
 
