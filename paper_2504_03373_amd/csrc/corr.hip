@@ -344,7 +344,7 @@ int resident_grid(K kernel, int n)
 // widened exactly to FP64 operands and the products accumulate in FP64.  With x = a + i b,
 //   Re K_ij += a_i a_j + b_i b_j,     Im K_ij += b_i a_j - a_i b_j
 // over k-steps of 4 frames: A[i][k] = x_{t+k}[16I + i] from lane i + 16k, B[k][j] = x_{t+k}[16J + j]
-// from lane j + 16k.  Each wave owns 16x16 tiles of the upper block triangle; the result goes
+// from lane j + 16k.  Each wave owns a 16x16 tile of the upper block triangle; the result goes
 // through LDS (the lower triangle as the conjugate of the same registers: K is Hermitian to the
 // bit, with a zero imaginary diagonal) and leaves in rows.  The FP64 result layout: element e of
 // lane l is row l/16 + 4e, column l%16 of the tile.
@@ -355,98 +355,110 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // noise_blend_c128).  R0 is read from R0f: Rf itself, or another matrix of the same shape.
 constexpr int kStore = 0, kAccumulate = 1, kBlend = 2;
 
+// A wave per tile of the upper triangle (10 at 64 channels: 2 or 3 per SIMD; with 4 waves two of
+// them had 3 tiles, and one wave per SIMD left every LDS read uncovered), the next chunk's frames and the
+// old K in flight under the products.  257 bins of 60 channels: 240 frames 60 us (69 us with 4 waves; a CU
+// with two of the bins has 33 us of MFMAs), the blends of 5 streams' 50 frames 71 us (82 us; 180 MB).
+template <int MP> struct F64Cfg {
+    static constexpr int NT = MP / 16;
+    static constexpr int WAVES = NT * (NT + 1) / 2 > 4 ? NT * (NT + 1) / 2 : 4;
+    static constexpr int THREADS = 64 * WAVES;
+};
+
 template <int MP>
 __device__ __forceinline__ void corr_f64_bin(const float2 *__restrict__ Xf, int T, int M,
                                              int64_t sT, double scale, int mode, double alpha,
                                              const double2 *R0f, double2 *Rf)
 {
-    constexpr int NT = MP / 16;
+    typedef F64Cfg<MP> C;
+    constexpr int NT = C::NT;
     constexpr int NTILE = NT * (NT + 1) / 2;
-    constexpr int TPW = (NTILE + 3) / 4;
     constexpr int S = MP + 16;                 // frame row stride: the 4 rows of a step on other banks
     constexpr int RS = MP + 1;                 // result row stride (complex128)
     constexpr int ZB = kChunk * S * 8, RB = MP * RS * 16;
+    constexpr int REGS = (kChunk * MP + C::THREADS - 1) / C::THREADS;
+    constexpr int ROWS = (MP + C::WAVES - 1) / C::WAVES;     // result rows of a wave
     __shared__ __attribute__((aligned(16))) char buf[ZB > RB ? ZB : RB];
     float2 *Z = reinterpret_cast<float2 *>(buf);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    doublex4 acc_re[TPW], acc_im[TPW];
+    auto load = [&](int t0, float2 (&v)[REGS]) {             // frame e / MP of the chunk, channel e % MP
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        acc_re[q] = doublex4{0.0, 0.0, 0.0, 0.0};
-        acc_im[q] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (int u = 0; u < REGS; ++u) {
+            const int e = tid + u * C::THREADS, tt = e / MP, m = e % MP;
+            v[u] = tt < kChunk && t0 + tt < T && m < M ? gload(Xf + (size_t)(t0 + tt) * sT + m)
+                                                       : make_float2(0.f, 0.f);
+        }
+    };
+    float2 v[REGS];
+    load(0, v);
+    double2 r0[ROWS];                                        // row wave + WAVES r, column lane
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = wave + C::WAVES * r;
+        r0[r] = mode != kStore && i < M && lane < M ? gload(R0f + (size_t)i * M + lane)
+                                                    : make_double2(0.0, 0.0);
     }
+    doublex4 acc_re = {0.0, 0.0, 0.0, 0.0}, acc_im = acc_re;
+    int I = 0, J = 0;
+    tile_coords(wave < NTILE ? wave : 0, NT, I, J);          // uniform
+    const int ca = 16 * I + (lane & 15), cb = 16 * J + (lane & 15);
     for (int t0 = 0; t0 < T; t0 += kChunk) {
-        const int nf = min(kChunk, T - t0);
-        float2 v[kChunkRegs<MP>];
-        load_chunk<MP>(Xf, t0, nf, M, sT, tid, v);               // every load in flight
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kChunkRegs<MP>; ++u) {               // frame e / MP, channel e % MP
-            const int e = tid + u * kThreads;
-            Z[(e / MP) * S + e % MP] = v[u];
+        for (int u = 0; u < REGS; ++u) {
+            const int e = tid + u * C::THREADS;
+            if (e < kChunk * MP) Z[(e / MP) * S + e % MP] = v[u];
         }
         __syncthreads();
-        const int nsteps = (nf + 3) >> 2;
-#pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            const int tile = wave + 4 * q;
-            if (tile < NTILE) {
-                int I, J;
-                tile_coords(tile, NT, I, J);
-                const int ca = 16 * I + (lane & 15), cb = 16 * J + (lane & 15);
-                for (int s = 0; s < nsteps; ++s) {
-                    const int row = (4 * s + (lane >> 4)) * S;
-                    const float2 a = Z[row + ca], b = Z[row + cb];
-                    const double ar = a.x, ai = a.y, br = b.x, bi = b.y;
-                    acc_re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, acc_re[q], 0, 0, 0);
-                    acc_re[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, bi, acc_re[q], 0, 0, 0);
-                    acc_im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acc_im[q], 0, 0, 0);
-                    acc_im[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ar, bi, acc_im[q], 0, 0, 0);
-                }
+        if (t0 + kChunk < T) load(t0 + kChunk, v);
+        const int nsteps = (min(kChunk, T - t0) + 3) >> 2;
+        if (wave < NTILE) {
+#pragma unroll 4
+            for (int s = 0; s < nsteps; ++s) {
+                const int row = (4 * s + (lane >> 4)) * S;
+                const float2 a = Z[row + ca], b = Z[row + cb];
+                const double ar = a.x, ai = a.y, br = b.x, bi = b.y;
+                acc_re = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, acc_re, 0, 0, 0);
+                acc_im = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acc_im, 0, 0, 0);
+                acc_re = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, bi, acc_re, 0, 0, 0);
+                acc_im = __builtin_amdgcn_mfma_f64_16x16x4f64(-ar, bi, acc_im, 0, 0, 0);
             }
         }
     }
     __syncthreads();                           // frames no longer needed: buf holds the result
     double2 *Rs = reinterpret_cast<double2 *>(buf);
+    if (wave < NTILE) {
+        const int j = 16 * J + (lane & 15);
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        const int tile = wave + 4 * q;
-        if (tile < NTILE) {
-            int I, J;
-            tile_coords(tile, NT, I, J);
-            const int j = 16 * J + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 16 * I + (lane >> 4) + 4 * e;
-                if (I == J && i > j) continue;           // mirrored from the (j, i) lane
-                const double vr = acc_re[q][e] * scale;
-                const double vi = (i == j) ? 0.0 : acc_im[q][e] * scale;
-                Rs[i * RS + j] = make_double2(vr, vi);
-                if (i != j) Rs[j * RS + i] = make_double2(vr, -vi);
-            }
+        for (int e = 0; e < 4; ++e) {
+            const int i = 16 * I + (lane >> 4) + 4 * e;
+            if (I == J && i > j) continue;                   // mirrored from the (j, i) lane
+            const double vr = acc_re[e] * scale;
+            const double vi = (i == j) ? 0.0 : acc_im[e] * scale;
+            Rs[i * RS + j] = make_double2(vr, vi);
+            if (i != j) Rs[j * RS + i] = make_double2(vr, -vi);
         }
     }
     __syncthreads();
-    for (int i = wave; i < M; i += kThreads / 64) {              // row by wave, column by lane
-        const int j = lane;
-        if (j >= M) continue;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {                         // row by wave, column by lane
+        const int i = wave + C::WAVES * r, j = lane;
+        if (i >= M || j >= M) continue;
         double2 v = Rs[i * RS + j];
         if (mode == kAccumulate) {
-            const double2 a = gload(R0f + (size_t)i * M + j);
-            v.x += a.x;
-            v.y += a.y;
+            v.x += r0[r].x;
+            v.y += r0[r].y;
         } else if (mode == kBlend) {
-            const double2 a = gload(R0f + (size_t)i * M + j);
-            v = make_double2(fma(alpha, a.x, (1.0 - alpha) * v.x),
-                             fma(alpha, a.y, (1.0 - alpha) * v.y));
+            v = make_double2(fma(alpha, r0[r].x, (1.0 - alpha) * v.x),
+                             fma(alpha, r0[r].y, (1.0 - alpha) * v.y));
         }
         gstore(Rf + (size_t)i * M + j, v);
     }
 }
 
 template <int MP>
-__global__ __launch_bounds__(kThreads) void corr_f64(const float2 *__restrict__ X, int T, int M,
+__global__ __launch_bounds__(F64Cfg<MP>::THREADS) void corr_f64(const float2 *__restrict__ X, int T, int M,
                                                      int64_t sF, int64_t sT, double scale,
                                                      int accumulate, double2 *__restrict__ R)
 {
@@ -458,7 +470,7 @@ __global__ __launch_bounds__(kThreads) void corr_f64(const float2 *__restrict__ 
 
 // Item (handle, bin): K[f] <- alpha Ks[f] + (1 - alpha) (1/T) sum_t x x^H of the handle's frames.
 template <int MP>
-__global__ __launch_bounds__(kThreads) void noise_corr_blend(const NoiseUpdDev *__restrict__ h,
+__global__ __launch_bounds__(F64Cfg<MP>::THREADS) void noise_corr_blend(const NoiseUpdDev *__restrict__ h,
                                                              const int2 *__restrict__ items,
                                                              double alpha)
 {
@@ -518,13 +530,13 @@ hipError_t launch_corr(const ssl_c64 *X, int F, int T, int M, int64_t sF, int64_
         const float2 *Xp = reinterpret_cast<const float2 *>(X);
         double2 *Rp = reinterpret_cast<double2 *>(R);
         if (M <= 16)
-            hipLaunchKernelGGL(corr_f64<16>, dim3(F), dim3(kThreads), 0, st, Xp, T, M, sF, sT,
+            hipLaunchKernelGGL(corr_f64<16>, dim3(F), dim3(F64Cfg<16>::THREADS), 0, st, Xp, T, M, sF, sT,
                                scale, accumulate, Rp);
         else if (M <= 32)
-            hipLaunchKernelGGL(corr_f64<32>, dim3(F), dim3(kThreads), 0, st, Xp, T, M, sF, sT,
+            hipLaunchKernelGGL(corr_f64<32>, dim3(F), dim3(F64Cfg<32>::THREADS), 0, st, Xp, T, M, sF, sT,
                                scale, accumulate, Rp);
         else
-            hipLaunchKernelGGL(corr_f64<64>, dim3(F), dim3(kThreads), 0, st, Xp, T, M, sF, sT,
+            hipLaunchKernelGGL(corr_f64<64>, dim3(F), dim3(F64Cfg<64>::THREADS), 0, st, Xp, T, M, sF, sT,
                                scale, accumulate, Rp);
         return hipGetLastError();
     }
@@ -541,13 +553,13 @@ hipError_t launch_noise_corr_blend(const NoiseUpdDev *h, const int2 *items, int 
 {
     if (n_items <= 0) return hipSuccess;
     if (cls == 16)
-        hipLaunchKernelGGL(noise_corr_blend<16>, dim3(n_items), dim3(kThreads), 0, st, h, items,
+        hipLaunchKernelGGL(noise_corr_blend<16>, dim3(n_items), dim3(F64Cfg<16>::THREADS), 0, st, h, items,
                            alpha);
     else if (cls == 32)
-        hipLaunchKernelGGL(noise_corr_blend<32>, dim3(n_items), dim3(kThreads), 0, st, h, items,
+        hipLaunchKernelGGL(noise_corr_blend<32>, dim3(n_items), dim3(F64Cfg<32>::THREADS), 0, st, h, items,
                            alpha);
     else
-        hipLaunchKernelGGL(noise_corr_blend<64>, dim3(n_items), dim3(kThreads), 0, st, h, items,
+        hipLaunchKernelGGL(noise_corr_blend<64>, dim3(n_items), dim3(F64Cfg<64>::THREADS), 0, st, h, items,
                            alpha);
     return hipGetLastError();
 }
