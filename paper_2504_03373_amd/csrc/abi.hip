@@ -1241,20 +1241,38 @@ ssl_status bdesc_reserve(ssl_ctx ctx, size_t bytes)
     return SSL_OK;
 }
 
-// Item lists of one kernel: blocks grouped by class (ascending), bins in order inside a block.
-void build_list(const std::vector<int> &cls_of_block, const std::vector<int> &F_of_block,
+// Item lists of one kernel: blocks grouped by class (ascending), bins in order inside a block.  A class of
+// the subspace iteration whose waves fill the chip (12 a CU) at most four times goes by groups of 8
+// bins instead, one block after the other within a group: the low bins, whose sources are the least resolved
+// and which take the most steps, then start first rather than once more with the last block, and the 8 XCDs
+// (workgroup i goes to XCD i mod 8) find a group's K^{-1} in their L2.  5 of 16 streams with 60 channels 162 ->
+// 130 us, their 16-channel ones 73 -> 61, 8 GEVD blocks 167 -> 145; with more rounds slow and fast bins mix
+// better block by block: 24 blocks 517 us against 531, a mixed batch of 60 channels 612 against 672.
+void build_list(const std::vector<int> &cls_of_block, const std::vector<int> &F_of_block, int cus,
                 int2 *out, std::vector<Seg> &segs)
 {
+    constexpr int kXcds = 8, kWavesPerCu = 12, kRounds = 4;
     std::vector<int> classes(cls_of_block);
     std::sort(classes.begin(), classes.end());
     classes.erase(std::unique(classes.begin(), classes.end()), classes.end());
     int pos = 0;
     for (int c : classes) {
         Seg s{c, pos, 0, 0};
-        for (size_t b = 0; b < cls_of_block.size(); ++b) {
-            if (cls_of_block[b] != c) continue;
-            for (int f = 0; f < F_of_block[b]; ++f) out[pos++] = make_int2((int)b, f);
-        }
+        std::vector<int> mb;
+        int Fmax = 0;
+        int64_t n = 0;
+        for (size_t b = 0; b < cls_of_block.size(); ++b)
+            if (cls_of_block[b] == c) {
+                mb.push_back((int)b);
+                Fmax = std::max(Fmax, F_of_block[b]);
+                n += F_of_block[b];
+            }
+        const bool grouped = c >= kIterClass && n * ((c - kIterClass + 15) / 16) <=
+                                                    (int64_t)kRounds * kWavesPerCu * cus;
+        const int step = grouped ? kXcds : Fmax;
+        for (int f0 = 0; f0 < Fmax; f0 += step)
+            for (int b : mb)
+                for (int f = f0; f < std::min(f0 + step, F_of_block[b]); ++f) out[pos++] = make_int2(b, f);
         s.count = pos - s.start;
         segs.push_back(s);
     }
@@ -1827,7 +1845,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         plan.max_dc = std::max(plan.max_dc, (int)((D + binsum_threads() - 1) / binsum_threads()));
         plan.max_fc = std::max(plan.max_fc, (int)nch);
     }
-    build_list(c_corr, Fs, hl, plan.corr);
+    build_list(c_corr, Fs, ctx->cu_count, hl, plan.corr);
     for (int cls : {16, 32, 64}) {                    // GEVD products: (block, bin) by class
         Seg sg{cls, 0, 0, 0};
         sg.start = plan.gevd.empty() ? 0 : plan.gevd.back().start + plan.gevd.back().count;
@@ -1902,7 +1920,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         // Jacobi items by class, then those of the subspace iteration by its classes, which are finer:
         // those of one Jacobi class are a contiguous run of items
         std::vector<Seg> segs;
-        build_list(c_jac, Fs, hl + 2 * n_items, segs);
+        build_list(c_jac, Fs, ctx->cu_count, hl + 2 * n_items, segs);
         for (Seg &sg : segs) {
             if (sg.cls < kIterClass) {
                 plan.jac.push_back(sg);
