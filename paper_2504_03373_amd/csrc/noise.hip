@@ -23,73 +23,122 @@ template <int L>
 __device__ __forceinline__ double row_bcast(double v)
 {
     const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + L, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + L, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+    const long long r = __builtin_amdgcn_update_dpp(0ll, b, 0x150 + L, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, r);
 }
 
 // K^{-1} of one bin by in-place Gauss-Jordan elimination in blocks of 16 pivots, NW waves (M <= 16 NW),
 // wave w holding rows 16 w .. 16 w + 15 as NW tiles in the FP64 MFMA result layout (element e of lane l:
-// row l / 16 + 4 e, column l % 16).  Block step k with P = W_kk, after which W_kk = P^{-1}:
-//   W_kj = P^{-1} W_kj,  W_ij -= W_ik W_kj,  W_ik = -W_ik P^{-1}    (i, j != k).
-// Every wave posts its tile of block column k and wave k its rows; wave k inverts P alone (16 scalar
-// steps, one wave, no barrier: row and column of the pivot by lane broadcasts), wave j forms
-// W_kj and its W_jk, and each wave updates its tiles on v_mfma_f64_16x16x4f64 (four real products
-// per complex one).  A product with the explicit P^{-1} has an error of 2^-53 cond(P) that the update's
-// W_ik (large where P is) would amplify once more, so P^{-1} W_kj is corrected once by its residual
-// W_kj - P (P^{-1} W_kj), which leaves the error of a backward stable solve (P-bar error at cond(K) =
-// 1e8: 6e-3 without the correction, 2e-7 with it and with scalar pivots).  The scalar pivots are the Schur-complement diagonals d_k = L_kk^2 as without blocks; one
-// that is <= 2^-40 max_i K_ii or not finite marks the bin NOT_PD (the inverse is then zero).
-// Padding rows and columns (>= M) are zero and stay zero.
-//   Bound by the 16-step chain of the pivot blocks (about half of the cycles) and the FP64 matrix cores.
-// 257 bins of 60 channels: 52 us, five such sets in one launch 148 us, 11 of 16 and 8 channels 14 us
-// (122, 346 and 31 us with one barrier per scalar pivot and rank-1 updates on the vector ALU).
+// row l / 16 + 4 e, column l % 16).  Block step k with P = W_kk = L U (L lower triangular with the
+// Schur-complement pivots on its diagonal, U upper with ones):
+//   wave k    factors P, 16 scalar steps in one wave (row and column of the pivot by lane exchanges);
+//   wave j    takes its tiles of the block row and the block column through the same steps by substitution,
+//             W~_j = L^{-1} W_kj and C~_j = W_jk U^{-1}; wave k the identity: L^{-1}, U^{-1};
+//   then, on v_mfma_f64_16x16x4f64 (four real products per complex one),
+//             W_ij -= C~_i W~_j,  W_kj = U^{-1} W~_j,  W_jk = -C~_j L^{-1},  W_kk = U^{-1} L^{-1}.
+// These are the scalar elimination's own sums, 16 pivots at a time.  No product is formed with an explicit
+// P^{-1}, whose error of 2^-53 cond(P) the large W_jk would multiply once more: |K^{-1} K - I| is about 2^-53
+// cond(K), as with scalar pivots (17 to 64 channels, one to three directional noises or a diffuse one, cond(K)
+// up to 1e11; with W_kj = P^{-1} W_kj, corrected once by its residual, 1e6 times as much at 1e8).  A pivot
+// that is <= 2^-40 max_i K_ii or not finite marks the bin NOT_PD (the inverse is then zero).  Padding rows
+// and columns (>= M) are zero and stay zero, but for ones on the diagonal (their pivots count as 1).
+//   Bound by the two chains of 16 steps (of P and of the substitution) and the FP64 matrix cores, about a third
+// each.  257 bins of 60 channels: 54 us, five such sets in one launch 150 us (122 and 346 us with one barrier per
+// scalar pivot and rank-1 updates on the vector ALU); 257 bins of up to 16 channels 8 us, of 32 channels 20 us.
 template <int NW> struct FactorCfg {
     static constexpr int THREADS = 64 * NW;
     static constexpr int LD = 16 * NW + 1;         // LDS row stride, complex128
 };
 
-// One scalar step (pivot KK of the block) on a 16 x 16 tile of one wave.
-template <int KK>
-__device__ __forceinline__ void pivot_step(double2 (&a)[4], int lane, double thr, int m, bool &bad)
+// The factors of a pivot block, [pivot s][i], zero elsewhere: column s of L below the diagonal over -p_s and
+// row s of U right of it, for the substitution; the inverses L^{-1} (row s) and U^{-1} (column s); 1 / p_s.
+constexpr int kPivLd = 17;
+struct PivotBlock {
+    double2 low[16 * kPivLd], up[16 * kPivLd], linv[16 * kPivLd], uinv[16 * kPivLd];
+    double ip[16];
+};
+
+// Lane group G (of 16 lanes) of a wave to all four.
+template <int G>
+__device__ __forceinline__ int group_bcast(int v)
 {
-    constexpr int E = KK >> 2, G = (KK & 3) << 4;
-    if (KK >= m || bad) return;                        // uniform
-    const double2 rowk = make_double2(__shfl(a[E].x, G | (lane & 15)), __shfl(a[E].y, G | (lane & 15)));
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const int h = (G & 1) ? a[1] : a[0];               // groups (0, 0, 2, 2) or (1, 1, 3, 3)
+    const auto b = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return (G & 2) ? b[1] : b[0];
+}
+template <int G>
+__device__ __forceinline__ double group_bcast(double v)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = group_bcast<G>((int)b), hi = group_bcast<G>((int)(b >> 32));
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Step S of the factorization on the tile of one wave: the entries below and right of pivot S; its column
+// and (unscaled) row stay as they are.  No branches, so that the steps overlap: a pivot that fails clears
+// ok, those of padding rows (S >= m) count as 1.  ipl: lane l's is that of pivot l % 16, inverted.
+template <int S>
+__device__ __forceinline__ void pivot_step(double2 (&a)[4], int lane, double thr, int m, bool &ok,
+                                           double &ipl)
+{
+    constexpr int E = S >> 2, G = S & 3;
     const long long pb = __builtin_bit_cast(long long, a[E].x);
-    const int lo = __builtin_amdgcn_readlane((int)pb, G | KK);
-    const int hi = __builtin_amdgcn_readlane((int)(pb >> 32), G | KK);
-    const double p = __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-    if (!(p > thr && p < 1.7e308)) {                   // NaN and Inf too
-        bad = true;
-        return;
-    }
+    const int lo = __builtin_amdgcn_readlane((int)pb, 16 * G + S);
+    const int hi = __builtin_amdgcn_readlane((int)(pb >> 32), 16 * G + S);
+    double p = __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+    p = S < m ? p : 1.0;
+    ok = ok && (S >= m || (p > thr && p < 1.7e308));   // not NaN or Inf either
     double ip = __builtin_amdgcn_rcp(p);
     ip = fma(ip, fma(-p, ip, 1.0), ip);
     ip = fma(ip, fma(-p, ip, 1.0), ip);
-    const double2 wk = make_double2(rowk.x * ip, rowk.y * ip);      // the pivot row, scaled
-    const bool colk = (lane & 15) == KK;
+    ipl = (lane & 15) == S ? ip : ipl;
+    if constexpr (S < 15) {
+        const bool right = (lane & 15) > S;
+        const double w = right ? ip : 0.0;
+        // the pivot row over -p, zero up to the pivot
+        const double wx = -group_bcast<G>(a[E].x) * w, wy = -group_bcast<G>(a[E].y) * w;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const double2 c = make_double2(row_bcast<KK>(a[e].x), row_bcast<KK>(a[e].y));   // W_ik
-        // selects by component: on whole double2 values the compiler goes through scratch memory
-        const double gx = fma(-c.x, wk.x, fma(c.y, wk.y, a[e].x));
-        const double gy = fma(-c.x, wk.y, fma(-c.y, wk.x, a[e].y));
-        double nx = colk ? -c.x * ip : gx, ny = colk ? -c.y * ip : gy;
-        if (e == E) {
-            const bool rowe = (lane & 48) == G;
-            nx = rowe ? (colk ? ip : wk.x) : nx;
-            ny = rowe ? (colk ? 0.0 : wk.y) : ny;
+        for (int e = E; e < 4; ++e) {
+            double cx = row_bcast<S>(a[e].x), cy = row_bcast<S>(a[e].y);       // W_is
+            if (e == E) {
+                const bool below = (lane >> 4) > G;
+                cx = below ? cx : 0.0;
+                cy = below ? cy : 0.0;
+            }
+            a[e].x = fma(cx, wx, fma(-cy, wy, a[e].x));
+            a[e].y = fma(cx, wy, fma(cy, wx, a[e].y));
         }
-        a[e].x = nx;
-        a[e].y = ny;
     }
 }
-template <int... KK>
-__device__ __forceinline__ void invert_tile(std::integer_sequence<int, KK...>, double2 (&a)[4],
-                                            int lane, double thr, int m, bool &bad)
+template <int... S>
+__device__ __forceinline__ void factor_tile(std::integer_sequence<int, S...>, double2 (&a)[4],
+                                            int lane, double thr, int m, bool &ok, double &ipl)
 {
-    (pivot_step<KK>(a, lane, thr, m, bad), ...);
+    (pivot_step<S>(a, lane, thr, m, ok, ipl), ...);
+}
+
+// Step S of the substitution on b, a tile of the block row transposed (element e: column l / 16 + 4 e, pivot
+// l % 16), and c, one of the block column (row l / 16 + 4 e, pivot l % 16): only the pivots after S change.
+template <int S>
+__device__ __forceinline__ void panel_step(double2 (&b)[4], double2 (&c)[4], int cl, const PivotBlock &pv)
+{
+    const double2 m = pv.low[S * kPivLd + cl], w = pv.up[S * kPivLd + cl];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double2 r = make_double2(row_bcast<S>(b[e].x), row_bcast<S>(b[e].y));
+        const double2 u = make_double2(row_bcast<S>(c[e].x), row_bcast<S>(c[e].y));
+        b[e].x = fma(r.x, m.x, fma(-r.y, m.y, b[e].x));
+        b[e].y = fma(r.x, m.y, fma(r.y, m.x, b[e].y));
+        c[e].x = fma(u.x, w.x, fma(-u.y, w.y, c[e].x));
+        c[e].y = fma(u.x, w.y, fma(u.y, w.x, c[e].y));
+    }
+}
+template <int... S>
+__device__ __forceinline__ void panel_steps(std::integer_sequence<int, S...>, double2 (&b)[4],
+                                            double2 (&c)[4], int cl, const PivotBlock &pv)
+{
+    (panel_step<S>(b, c, cl, pv), ...);
 }
 
 // out = init + sign * X y on one 16 x 16 complex tile, K = 16: x(q) the A operand of k-step q (row
@@ -124,8 +173,10 @@ __device__ __forceinline__ void noise_factor_bin(const double2 *__restrict__ Kf,
                                                  int32_t *__restrict__ stf, int M)
 {
     typedef FactorCfg<NW> C;
-    __shared__ double2 rowp[16 * C::LD];           // [pivot][column]: block row k, then P^{-1} of it
-    __shared__ double2 colp[16 * C::LD];           // [pivot][row]: block column k
+    constexpr int kPanel = NW > 1 ? 16 * C::LD : 1;
+    __shared__ double2 rowp[kPanel];               // [pivot][column]: block row k, then W~
+    __shared__ double2 colp[kPanel];               // [pivot][row]: C~, each wave its own rows
+    __shared__ PivotBlock pv;
     __shared__ double dmax_s[NW];
     __shared__ int bad_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -153,6 +204,7 @@ __device__ __forceinline__ void noise_factor_bin(const double2 *__restrict__ Kf,
     }
     if (lane == 0) dmax_s[wave] = dm;
     if (tid == 0) bad_s = 0;
+    for (int i = tid; i < 16 * kPivLd; i += C::THREADS) pv.low[i] = pv.up[i] = make_double2(0.0, 0.0);
     __syncthreads();
     dm = 0.0;
     bool fin = true;
@@ -169,68 +221,75 @@ __device__ __forceinline__ void noise_factor_bin(const double2 *__restrict__ Kf,
 #pragma unroll 1
     for (int k = 0; k < NW; ++k) {
         if (k < nb && !bad) {                          // uniform
-            const int ow = 16 * wave, ok = 16 * k;
-            // block column k from every wave, block row k from wave k
-#pragma unroll
-            for (int e = 0; e < 4; ++e) colp[cl * C::LD + ow + kl + 4 * e] = a[0][e];
-            if (wave == k) {
-                invert_tile(std::make_integer_sequence<int, 16>(), a[0], lane, thr, M - ok, bad);
-                if (bad && lane == 0) bad_s = 1;
-#pragma unroll
-                for (int j = 0; j < NW; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        rowp[(kl + 4 * e) * C::LD + 16 * ((j + k) % NW) + cl] = a[j][e];
-            }
-            __syncthreads();
-            bad = bad_s != 0;
-            double2 v[4];                              // V^T, element e: (pivot kl + 4 e, row cl)
-            if (wave != k && !bad) {
-                // W_kj = P^{-1} W_kj (j = wave), corrected by its residual
-                double2 r0[4], w[4], r[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) r0[e] = rowp[(kl + 4 * e) * C::LD + ow + cl];
-                auto inv = [&](int q) { return rowp[cl * C::LD + ok + 4 * q + kl]; };
-                mul_add([](int) { return make_double2(0.0, 0.0); }, inv, r0, 1.0, w);
-                mul_add([&](int e) { return r0[e]; },
-                        [&](int q) { return colp[(4 * q + kl) * C::LD + ok + cl]; }, w, -1.0, r);
-                mul_add([&](int e) { return w[e]; }, inv, r, 1.0, w);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)            // tile `wave` of the panel: read by this wave alone
-                    rowp[(kl + 4 * e) * C::LD + ow + cl] = w[e];
-                // V = W_ik P^{-1} (i = wave) as V^T = P^{-T} W_ik^T
-#pragma unroll
-                for (int e = 0; e < 4; ++e) r0[e] = colp[(kl + 4 * e) * C::LD + ow + cl];
-                auto invt = [&](int q) { return rowp[(4 * q + kl) * C::LD + ok + cl]; };
-                mul_add([](int) { return make_double2(0.0, 0.0); }, invt, r0, 1.0, v);
-            }
-            __syncthreads();
+            const int ow = 16 * wave;
             if (wave == k) {
 #pragma unroll
                 for (int j = 1; j < NW; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        a[j][e] = rowp[(kl + 4 * e) * C::LD + 16 * ((j + k) % NW) + cl];
-            } else if (!bad) {
-                auto cop = [&](int q) { return colp[(4 * q + kl) * C::LD + ow + cl]; };
+                        rowp[(kl + 4 * e) * C::LD + 16 * ((j + k) % NW) + cl] = a[j][e];
+                bool ok = true;
+                double ipc = 0.0;                      // 1 / p of pivot cl
+                factor_tile(std::make_integer_sequence<int, 16>(), a[0], lane, thr, M - 16 * k, ok, ipc);
+                if (!ok && lane == 0) bad_s = 1;
+                if (lane < 16) pv.ip[lane] = ipc;
 #pragma unroll
-                for (int j = 1; j < NW; ++j) {         // W_ij -= W_ik W_kj
-                    double2 y[4];
+                for (int e = 0; e < 4; ++e) {          // entry (i, cl): of L below, of U right of the diagonal
+                    const int i = kl + 4 * e;
+                    const double sc = i > cl ? -ipc : i < cl ? -pv.ip[i] : 0.0;
+                    double2 *to = i > cl ? pv.low + cl * kPivLd + i : pv.up + i * kPivLd + cl;
+                    *to = make_double2(a[0][e].x * sc, a[0][e].y * sc);
+                }
+            }
+            __syncthreads();
+            bad = bad_s != 0;
+            double2 b[4], c[4];
+            if (!bad) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double one = kl + 4 * e == cl ? 1.0 : 0.0;
+                    b[e] = c[e] = make_double2(one, 0.0);
+                    if (NW > 1 && wave != k) {
+                        b[e] = rowp[cl * C::LD + ow + kl + 4 * e];
+                        c[e] = a[0][e];
+                    }
+                }
+                panel_steps(std::make_integer_sequence<int, 15>(), b, c, cl, pv);
+                // tile `wave` of the panels is read by this wave alone so far
+                const double ip = pv.ip[cl];
+                double2 *lb = wave == k ? pv.linv + cl * kPivLd : rowp + cl * C::LD + ow;
+                double2 *cb = wave == k ? pv.uinv + cl * kPivLd : colp + cl * C::LD + ow;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    lb[kl + 4 * e] = make_double2(b[e].x * ip, b[e].y * ip);
+                    cb[kl + 4 * e] = c[e];
+                }
+            }
+            __syncthreads();
+            if (!bad) {
+                const bool own = wave == k;
+                auto row = [&](int j, double2 (&y)[4]) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         y[q] = rowp[(4 * q + kl) * C::LD + 16 * ((j + k) % NW) + cl];
-                    mul_add([&](int e) { return a[j][e]; }, cop, y, -1.0, a[j]);
-                }
-                // W_ik = -V: the transpose through this wave's part of colp
+                };
+                const double2 *op = own ? pv.uinv + kl * kPivLd + cl : colp + kl * C::LD + ow + cl;
+                const int step = 4 * (own ? kPivLd : C::LD);
+                const double sign = own ? 1.0 : -1.0;
+                double2 x[4], y[4];                    // U^{-1} or C~
 #pragma unroll
-                for (int e = 0; e < 4; ++e) colp[(kl + 4 * e) * C::LD + ow + cl] = v[e];
+                for (int q = 0; q < 4; ++q) x[q] = op[q * step];
+                auto left = [&](int q) { return x[q]; };
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double2 x = colp[cl * C::LD + ow + kl + 4 * e];
-                    a[0][e] = make_double2(-x.x, -x.y);
+                for (int j = 1; j < NW; ++j) {
+                    row(j, y);
+                    mul_add([&](int e) { return own ? make_double2(0.0, 0.0) : a[j][e]; }, left, y, sign, a[j]);
                 }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) y[q] = pv.linv[(4 * q + kl) * kPivLd + cl];
+                mul_add([](int) { return make_double2(0.0, 0.0); }, left, y, sign, a[0]);
             }
-            __syncthreads();                           // rowp and colp have been read
+            __syncthreads();                           // rowp and the pivot block have been read
         }
         if constexpr (NW > 1) {
             double2 t[4];

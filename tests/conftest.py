@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -12,6 +13,13 @@ if ROOT not in sys.path:
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (gfx950) GPU and the built HIP library")
     config.addinivalue_line("markers", "slow: longer CPU test")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _no_garbage_of_other_modules():
+    """Tensors in reference cycles of an earlier module are freed now, not while a test of this one
+    looks at the amount of memory allocated."""
+    gc.collect()
 
 
 @pytest.fixture(scope="session")

@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import numpy as np
+import pytest
 
 U32 = 2.0 ** -24     # FP32 unit roundoff
 
@@ -86,3 +87,20 @@ def peak_ambiguity(Pbar: np.ndarray, n_el: int, n_az: int, Ns: int, rtol: float)
 def peaks_ambiguous(Pbar: np.ndarray, n_el: int, n_az: int, Ns: int, rtol: float) -> bool:
     """True when a relative perturbation of rtol could change the returned peaks."""
     return bool(peak_ambiguity(Pbar, n_el, n_az, Ns, rtol))
+
+
+@pytest.fixture(scope="module")
+def S():
+    """The package, its library loaded; a GPU test without a GPU is an error."""
+    import torch
+    import paper_2504_03373_amd as pkg
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pkg.lib()
+    return pkg
+
+
+@pytest.fixture(scope="module")
+def ctx(S):
+    c = S.ssl_ctx_create(0, 0)
+    yield c
+    S.ssl_ctx_destroy(c)
