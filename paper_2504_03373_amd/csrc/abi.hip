@@ -326,8 +326,7 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
     ssl_c64 *En = reinterpret_cast<ssl_c64 *>(w + 2 * L.bR);
     float *P = reinterpret_cast<float *>(w + 2 * L.bR + L.bE);
     float *Pb = Pbar ? Pbar : reinterpret_cast<float *>(w + 2 * L.bR + L.bE + L.bP);
-    int32_t *stt = bin_status ? bin_status
-                              : reinterpret_cast<int32_t *>(w + 2 * L.bR + L.bE + L.bP + L.bB);
+    int32_t *stt = reinterpret_cast<int32_t *>(w + 2 * L.bR + L.bE + L.bP + L.bB);
     auto run = [&](int id, auto &&launch) {
         return may_time ? timed(ctx, id, st, launch) : launch();
     };
@@ -335,6 +334,9 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
     const bool gevd = use_gevd(ctx, K);
     const bool sig = use_sig(ctx, M, p, Ns, gevd);
     const bool iter = use_iteration(ctx, sig, false);
+    // the iteration hands bins to the Jacobi solve by their status, so that is workspace: the caller's array
+    // gets the final ones only
+    if (bin_status && !iter) stt = bin_status;
     if (gevd) {
         e = run(SSL_K_WHITEN, [&] { return launch_gevd_whiten(K->Kisq, R, A, F, M, st); });
         if (e != hipSuccess) return hip_fail(e, "GEVD whitening launch");
@@ -351,11 +353,11 @@ ssl_status localize_corr_enqueue(ssl_ctx ctx, bool may_time, char *w, const Loca
     e = run(SSL_K_JACOBI, [&] {
         if (iter) {
             const hipError_t le = launch_subspace(K && !gevd ? K->Kinv : nullptr, K ? K->status : nullptr,
-                                                  gevd ? A : R, A, F, M, Ns, stt, Es, Esl, st);
+                                                  gevd ? A : R, A, F, M, Ns, stt, bin_status, Es, Esl, st);
             if (le != hipSuccess) return le;
             return launch_jacobi(A, K ? K->status : nullptr, F, M, Ns, SSL_DEFAULT_SWEEPS,
                                  jac_lanes(ctx, M), nullptr, nullptr, stt, nullptr, st, nullptr,
-                                 sub_full_for(ctx, p, false), Es, Esl, true);
+                                 sub_full_for(ctx, p, false), Es, Esl, true, bin_status);
         }
         // through the signal subspace the noise vectors are neither formed nor stored
         return launch_svd(ctx, A, K ? K->status : nullptr, F, M, Ns, SSL_DEFAULT_SWEEPS,
@@ -1826,7 +1828,9 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         w += align256(F * D * sizeof(float));
         B.part = reinterpret_cast<float *>(w);
         w += align256(nch * D * sizeof(float));
-        B.status = d.bin_status ? d.bin_status : reinterpret_cast<int32_t *>(w);
+        // (blocks may share a status array: not where it hands bins over)
+        B.status = d.bin_status && !iterb[b] ? d.bin_status : reinterpret_cast<int32_t *>(w);
+        B.status_out = iterb[b] ? d.bin_status : nullptr;
         w += align256(F * sizeof(int32_t));
         B.Pbar = d.Pbar ? d.Pbar : reinterpret_cast<float *>(w);
         w += align256(D * sizeof(float));

@@ -602,7 +602,8 @@ __device__ __forceinline__ float wave_sum(float v)
 // signal vectors without Q below).  Lf ([6], with Esf, Ns <= 3,
 // or null): the inverse L^{-1} of the Cholesky factor of their Gram matrix E_s^H E_s, computed in
 // FP64 from the stored complex64 values, lower triangle by rows (00, 10, 11, 20, 21, 22), zero if
-// the bin failed: the projector onto span E_s is E_s (E_s^H E_s)^{-1} E_s^H exactly.
+// the bin failed: the projector onto span E_s is E_s (E_s^H E_s)^{-1} E_s^H exactly.  outf: the caller's
+// copy of the status, or null.
 template <int MP, int G>
 __device__ __forceinline__ void jacobi_bin(float2 *__restrict__ Af, int kst, int M, int Ns,
                                            int max_sweeps, float2 *__restrict__ Enf,
@@ -610,7 +611,8 @@ __device__ __forceinline__ void jacobi_bin(float2 *__restrict__ Af, int kst, int
                                            int32_t *__restrict__ convf,
                                            float2 *__restrict__ Uf = nullptr, int sub_full = -1,
                                            float2 *__restrict__ Esf = nullptr,
-                                           double2 *__restrict__ Lf = nullptr)
+                                           double2 *__restrict__ Lf = nullptr,
+                                           int32_t *__restrict__ outf = nullptr)
 {
     typedef JacobiCfg<MP, G> C;
     constexpr int R = C::R;
@@ -1376,6 +1378,7 @@ __device__ __forceinline__ void jacobi_bin(float2 *__restrict__ Af, int kst, int
         }
     if (tid == 0) {
         if (stf != nullptr) *stf = st;
+        if (outf != nullptr) *outf = st;
         if (convf != nullptr) {
             convf[0] = sweeps;
             convf[1] = rot_total;
@@ -1391,7 +1394,7 @@ __global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS)) void jacobi_svd(
     float2 *__restrict__ A, const int32_t *__restrict__ kstatus, int M, int Ns, int max_sweeps,
     float2 *__restrict__ En, float *__restrict__ sigma, int32_t *__restrict__ bin_status,
     int32_t *__restrict__ conv, float2 *__restrict__ U, int sub_full, float2 *__restrict__ Es,
-    double2 *__restrict__ Esl, bool pending)
+    double2 *__restrict__ Esl, bool pending, int32_t *__restrict__ status_out)
 {
     const int f = blockIdx.x;
     if (pending && bin_status[f] != SSL_BIN_PENDING) return;    // uniform: the bin is solved
@@ -1400,7 +1403,8 @@ __global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS)) void jacobi_svd(
                       sigma ? sigma + (size_t)f * M : nullptr,
                       bin_status ? bin_status + f : nullptr, conv ? conv + 3 * f : nullptr,
                       U ? U + (size_t)f * M * M : nullptr, sub_full,
-                      Es ? Es + (size_t)f * Ns * M : nullptr, Esl ? Esl + 6 * (size_t)f : nullptr);
+                      Es ? Es + (size_t)f * Ns * M : nullptr, Esl ? Esl + 6 * (size_t)f : nullptr,
+                      status_out ? status_out + f : nullptr);
 }
 
 // Persistent: a fixed grid of workgroups draws (block, bin) items from a device counter until the
@@ -1474,7 +1478,8 @@ __attribute__((amdgpu_waves_per_eu(JacobiCfg<MP, G>::WAVES_PER_EU))) void jacobi
                               Ns, max_sweeps, nullptr, nullptr, stats ? nullptr : B.status + f,
                               B.conv ? B.conv + 3 * (size_t)f : nullptr, nullptr, sub_full,
                               stats ? nullptr : B.Es + (size_t)f * Ns * M,
-                              stats ? nullptr : B.Esl + 6 * (size_t)f);
+                              stats ? nullptr : B.Esl + 6 * (size_t)f,
+                              !stats && B.status_out ? B.status_out + f : nullptr);
         }
     }
 }
@@ -1731,13 +1736,14 @@ __global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS)) void jacobi_warm(
 template <int MP, int G>
 hipError_t launch_cfg(ssl_c64 *A, const int32_t *kstatus, int F, int M, int Ns, int max_sweeps,
                       ssl_c64 *En, float *sigma, int32_t *bin_status, int32_t *conv, ssl_c64 *U,
-                      int sub_full, ssl_c64 *Es, ssl_c128 *Esl, bool pending, hipStream_t st)
+                      int sub_full, ssl_c64 *Es, ssl_c128 *Esl, bool pending, int32_t *status_out,
+                      hipStream_t st)
 {
     hipLaunchKernelGGL((jacobi_svd<MP, G>), dim3(F), dim3(JacobiCfg<MP, G>::THREADS), 0, st,
                        reinterpret_cast<float2 *>(A), kstatus, M, Ns, max_sweeps,
                        reinterpret_cast<float2 *>(En), sigma, bin_status, conv,
                        reinterpret_cast<float2 *>(U), sub_full, reinterpret_cast<float2 *>(Es),
-                       reinterpret_cast<double2 *>(Esl), pending);
+                       reinterpret_cast<double2 *>(Esl), pending, status_out);
     return hipGetLastError();
 }
 
@@ -1820,12 +1826,12 @@ int jacobi_persistent_wg_per_cu(int cls, int lanes)
 hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int Ns, int max_sweeps,
                          int lanes, ssl_c64 *En, float *sigma, int32_t *bin_status, int32_t *conv,
                          hipStream_t st, ssl_c64 *U, int sub_full, ssl_c64 *Es, ssl_c128 *Esl,
-                         bool pending)
+                         bool pending, int32_t *status_out)
 {
     hipError_t e = hipErrorInvalidValue;
     dispatch(jacobi_class(M), lanes, [&]<int MP, int G>() {
         e = launch_cfg<MP, G>(A, kstatus, F, M, Ns, max_sweeps, En, sigma, bin_status, conv, U,
-                              sub_full, Es, Esl, pending, st);
+                              sub_full, Es, Esl, pending, status_out, st);
     });
     return e;
 }

@@ -114,7 +114,9 @@ struct BlockDev {
     float2 *Es;                     // signal vectors [F][Ns][M] (workspace) or null
     double2 *Esl;                   // per bin: L^{-1} of their Gram matrix's Cholesky factor, [F][6]
     float *P, *part;
-    int32_t *peaks, *status;        // caller outputs
+    int32_t *peaks;                 // caller outputs
+    int32_t *status;                // per bin: the caller's, or workspace (also where it hands bins over
+    int32_t *status_out;            // from one launch to the next; then the caller's copy, or null)
     float *peak_val, *Pbar;
     int32_t *conv;                  // [F][3] Jacobi statistics or null
 };
@@ -266,14 +268,15 @@ hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int N
                          int max_sweeps, int lanes, ssl_c64 *En, float *sigma,
                          int32_t *bin_status, int32_t *conv, hipStream_t st,
                          ssl_c64 *U = nullptr, int sub_full = -1, ssl_c64 *Es = nullptr,
-                         ssl_c128 *Esl = nullptr, bool pending = false);
+                         ssl_c128 *Esl = nullptr, bool pending = false, int32_t *status_out = nullptr);
 // Signal vectors by block subspace iteration (subspace.hip, Ns <= 3): Es,
 // Esl and status SSL_BIN_OK, or status SSL_BIN_PENDING and A = K^{-1} R (A itself where Kinv is
 // null: R) for the Jacobi solve that has to follow -- launch_jacobi with pending, or
-// launch_jacobi_pending over the same items (whose blocks all have Es and p = 2).
+// launch_jacobi_pending over the same items (whose blocks all have Es and p = 2).  bin_status is workspace;
+// status_out (optional): the caller's copy of the final statuses.
 hipError_t launch_subspace(const ssl_c128 *Kinv, const int32_t *kstatus, const ssl_c64 *R,
-                           ssl_c64 *A, int F, int M, int Ns, int32_t *bin_status, ssl_c64 *Es,
-                           ssl_c128 *Esl, hipStream_t st);
+                           ssl_c64 *A, int F, int M, int Ns, int32_t *bin_status,
+                           int32_t *status_out, ssl_c64 *Es, ssl_c128 *Esl, hipStream_t st);
 hipError_t launch_subspace_batch(const BlockDev *blk, const int2 *items, int n_items, int cls,
                                  hipStream_t st);
 hipError_t launch_jacobi_pending(const BlockDev *blk, const int2 *items, int n_items, int cls,

@@ -390,11 +390,13 @@ __device__ __forceinline__ void prepare_test(double2 t, int Ns, int lane, Sh &sh
 }
 
 // One bin.  Kf: K^{-1} of the bin ([M][M] FP64) or null (SEVD-MUSIC: A = R); Rf, Af: [M][M] complex64,
-// Af written only where the Jacobi solve will read it (never with Kf null: A is R there).
+// Af written only where the Jacobi solve will read it (never with Kf null: A is R there).  stf: the status
+// that the Jacobi solve looks at; outf: the caller's copy of a final one, or null.
 template <int NW, int KQ>
 __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int kst,
                                              const float2 *__restrict__ Rf, float2 *__restrict__ Af,
                                              int M, int Ns, bool keep_a, int32_t *__restrict__ stf,
+                                             int32_t *__restrict__ outf,
                                              float2 *__restrict__ Esf, double2 *__restrict__ Lf)
 {
     typedef SubShared<NW> Sh;
@@ -407,6 +409,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
 
     if (kst != SSL_BIN_OK) {                           // uniform: the noise set failed in this bin
         if (tid == 0) gstore(stf, (int32_t)kst);
+        if (tid == 0 && outf) gstore(outf, (int32_t)kst);
         return;
     }
     {
@@ -686,6 +689,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
         }
         gram(ef, ef, sh.part[wave][0]);
         if (tid == 0) gstore(stf, (int32_t)SSL_BIN_OK);
+        if (tid == 0 && outf) gstore(outf, (int32_t)SSL_BIN_OK);
         __syncthreads();
         if (wave == 0) {
             const double2 g = sum_parts(0);            // e_i^H e_j
@@ -717,12 +721,14 @@ template <int NW, int KQ>
 __global__ __launch_bounds__((SubCfg<NW, KQ>::THREADS)) void subspace_single(
     const double2 *__restrict__ Kinv, const int32_t *__restrict__ kstatus,
     const float2 *__restrict__ R, float2 *__restrict__ A, int M, int Ns,
-    int32_t *__restrict__ status, float2 *__restrict__ Es, double2 *__restrict__ Esl)
+    int32_t *__restrict__ status, int32_t *__restrict__ status_out, float2 *__restrict__ Es,
+    double2 *__restrict__ Esl)
 {
     const int f = blockIdx.x;
     const size_t o = (size_t)f * M * M;
     subspace_bin<NW, KQ>(Kinv ? Kinv + o : nullptr, kstatus ? kstatus[f] : SSL_BIN_OK, R + o, A + o,
-                         M, Ns, false, status + f, Es + (size_t)f * Ns * M, Esl + 6 * (size_t)f);
+                         M, Ns, false, status + f, status_out ? status_out + f : nullptr,
+                         Es + (size_t)f * Ns * M, Esl + 6 * (size_t)f);
 }
 
 // Item = (block, bin).
@@ -738,7 +744,7 @@ __attribute__((amdgpu_waves_per_eu(3))) void subspace_batch(
     const bool whiten = B.Kinv && !B.Kisq;             // GEVD: A = C = W R W is there already
     subspace_bin<NW, KQ>(whiten ? B.Kinv + o : nullptr, B.kstatus ? B.kstatus[f] : SSL_BIN_OK,
                          (B.Kisq ? B.A : B.R) + o, B.A + o, M, Ns, B.conv != nullptr, B.status + f,
-                         B.Es + (size_t)f * Ns * M, B.Esl + 6 * (size_t)f);
+                         B.status_out ? B.status_out + f : nullptr, B.Es + (size_t)f * Ns * M, B.Esl + 6 * (size_t)f);
 }
 
 // Calls fn.template operator()<NW, KQ>() for a subspace class.
@@ -759,14 +765,14 @@ hipError_t with_class(int cls, Fn &&fn)
 }  // namespace
 
 hipError_t launch_subspace(const ssl_c128 *Kinv, const int32_t *kstatus, const ssl_c64 *R,
-                           ssl_c64 *A, int F, int M, int Ns, int32_t *bin_status, ssl_c64 *Es,
-                           ssl_c128 *Esl, hipStream_t st)
+                           ssl_c64 *A, int F, int M, int Ns, int32_t *bin_status,
+                           int32_t *status_out, ssl_c64 *Es, ssl_c128 *Esl, hipStream_t st)
 {
     return with_class(subspace_class(M), [&]<int NW, int KQ>() {
         hipLaunchKernelGGL((subspace_single<NW, KQ>), dim3(F), dim3(SubCfg<NW, KQ>::THREADS), 0, st,
                            reinterpret_cast<const double2 *>(Kinv), kstatus,
                            reinterpret_cast<const float2 *>(R), reinterpret_cast<float2 *>(A), M,
-                           Ns, bin_status, reinterpret_cast<float2 *>(Es),
+                           Ns, bin_status, status_out, reinterpret_cast<float2 *>(Es),
                            reinterpret_cast<double2 *>(Esl));
         return hipGetLastError();
     });

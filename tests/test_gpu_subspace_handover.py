@@ -1,0 +1,63 @@
+"""What the subspace iteration (csrc/subspace.hip) hands over to the Jacobi solve behind it, and what the
+caller's bin_status sees of it.  MI355X only."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import S, ctx, to_dev, to_host  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def scene(F, M, T, grid, weak, seed):
+    """Two sources over a white floor, the second with `weak` of the first's amplitude; X and the steering
+    table.  No noise set: A is R."""
+    rng = np.random.default_rng(seed)
+    H = synth.steering_table(synth.circle_array(M), grid, synth.bin_freqs(257)[100:100 + F])
+    s = synth.cn(rng, (F, T, 2), 1.0) * np.array([1.0, weak])
+    X = s @ H[:, [grid.n_az // 3, 2 * grid.n_az // 3], :].astype(complex)
+    return (X + 1e-4 * synth.cn(rng, (F, T, M), 1.0)).astype(np.complex64), H
+
+
+def sigma(X):
+    """Singular values of R per bin."""
+    return np.linalg.svd(X.astype(complex), compute_uv=False) ** 2 / X.shape[1]
+
+
+def outs(F, D, Ns=2):
+    import torch
+    dev = "cuda:0"
+    return dict(pk=torch.full((Ns,), -7, dtype=torch.int32, device=dev),
+                pv=torch.zeros(Ns, dtype=torch.float32, device=dev),
+                Pbar=torch.zeros(D, dtype=torch.float32, device=dev),
+                st=torch.full((F,), -7, dtype=torch.int32, device=dev))
+
+
+@pytest.mark.parametrize("M", [8, 24, 60])
+def test_blocks_sharing_a_status_array(S, ctx, M):  # noqa: F811
+    """Two blocks of a batch write one bin_status: every bin of the first is left to the Jacobi solve, none
+    of the second, so that a hand-over in the caller's array would cross.  As with arrays of their own."""
+    import torch
+    F, T, grid = 37, 40, synth.DirectionGrid(24, 2)
+    hard, H = scene(F, M, T, grid, 0.02, M)
+    easy, _ = scene(F, M, T, grid, 0.7, M + 1)
+    th = sigma(hard) ** 2
+    assert np.all(th[:, 1] < 1e-6 * th[:, 0])          # below the ratio that the iteration decides
+    th = sigma(easy) ** 2
+    assert np.all(th[:, 1] > 1e-4 * th[:, 0]) and np.all(th[:, 2] < 1e-6 * th[:, 1])
+    Hd, Xd = to_dev(H), [to_dev(hard), to_dev(easy)]
+
+    def batch(share):
+        o = [outs(F, grid.n_az * grid.n_el) for _ in Xd]
+        if share:
+            o[1]["st"] = o[0]["st"]
+        S.ssl_localize_batch(ctx, [S.block_desc(x, None, Hd, grid.n_az, grid.n_el, 2, q["pk"], q["pv"], q["Pbar"],
+                                                q["st"]) for x, q in zip(Xd, o)], S.SSL_FP32, 2)
+        return [{k: to_host(v) for k, v in q.items()} for q in o]
+
+    own, shared = batch(False), batch(True)
+    for b in range(2):
+        assert np.all(own[b]["st"] == 0)
+        for k in own[b]:
+            assert np.array_equal(own[b][k], shared[b][k]), (b, k)
+    torch.cuda.synchronize()
