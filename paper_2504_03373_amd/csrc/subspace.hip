@@ -22,8 +22,9 @@
 // unit length with the inverse Cholesky factor of their FP64 Gram matrix, as the Jacobi solve does.
 //
 // A bin that this cannot decide -- no convergence in kMaxSteps steps, theta_Ns below 1e-6 theta_1 (it may
-// be beyond the numerical rank), magnitudes far from 1, anything not finite -- is marked
-// SSL_BIN_PENDING and its A stored: the Jacobi solve, launched next, takes those bins alone.
+// be beyond the numerical rank), anything not finite -- is marked SSL_BIN_PENDING and its A stored: the
+// Jacobi solve, launched next, takes those bins alone.  The magnitude of A does not matter: it is scaled by a
+// power of two first, and the result has unit length.
 //
 // What bounds it: the FP64 matrix cores (64 cycles per v_mfma_f64_16x16x4f64 and SIMD: about 11.5k
 // for A, 1.9k per FP64 product, 1.3k per step for the small matrices) and, with one block per launch,
@@ -63,7 +64,6 @@ constexpr int kDegree = 3;           // its degree
 constexpr double kWide = 152.0;
 constexpr double kTol = 5.9604644775390625e-08;      // 2^-24
 constexpr double kRange = 1e-6;      // theta_Ns / theta_1 below this: left to the Jacobi solve
-constexpr int kExpMin = -80, kExpMax = 100;   // max |A| outside 2^.. this: left to the Jacobi solve
 
 // NW waves, KQ k-steps of 4: M <= 16 NW and M <= 4 KQ
 template <int NW, int KQ> struct SubCfg {
@@ -619,7 +619,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
                 break;
             }
             const double th1 = sh.th1, thS = sh.thS;
-            if (step >= kMaxSteps || !(th1 > 0.0) || ex < kExpMin || ex > kExpMax) break;
+            if (step >= kMaxSteps || !(th1 > 0.0)) break;
             if (step >= kAccel && apart() && sh.thC > kRange * thS && (fresh || th1 <= kWide * thS)) {
                 // slow bin: the block filtered by the Chebyshev polynomial of A A^H on [0, thC], thC
                 // the smallest Ritz value: W_0 = V, W_1 = (a A A^H - 1) V, W_{k+1} = 2 (a A A^H - 1)

@@ -9,19 +9,26 @@ from gpu_util import S, ctx, to_dev, to_host  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-def scene(F, M, T, grid, weak, seed):
+def scene(F, M, T, grid, weak, seed, floor=1e-4):
     """Two sources over a white floor, the second with `weak` of the first's amplitude; X and the steering
     table.  No noise set: A is R."""
     rng = np.random.default_rng(seed)
     H = synth.steering_table(synth.circle_array(M), grid, synth.bin_freqs(257)[100:100 + F])
     s = synth.cn(rng, (F, T, 2), 1.0) * np.array([1.0, weak])
     X = s @ H[:, [grid.n_az // 3, 2 * grid.n_az // 3], :].astype(complex)
-    return (X + 1e-4 * synth.cn(rng, (F, T, M), 1.0)).astype(np.complex64), H
+    return (X + floor * synth.cn(rng, (F, T, M), 1.0)).astype(np.complex64), H
 
 
 def sigma(X):
     """Singular values of R per bin."""
     return np.linalg.svd(X.astype(complex), compute_uv=False) ** 2 / X.shape[1]
+
+
+def single(S, ctx, X, H, grid):  # noqa: F811
+    o = outs(X.shape[0], grid.n_az * grid.n_el)
+    S.ssl_localize(ctx, to_dev(X), None, to_dev(H), S.SSL_FP32, grid.n_az, grid.n_el, 2, 2, o["pk"], o["pv"],
+                   o["Pbar"], o["st"])
+    return {k: to_host(v) for k, v in o.items()}
 
 
 def outs(F, D, Ns=2):
@@ -61,3 +68,17 @@ def test_blocks_sharing_a_status_array(S, ctx, M):  # noqa: F811
         for k in own[b]:
             assert np.array_equal(own[b][k], shared[b][k]), (b, k)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M", [8, 24, 60])
+def test_any_magnitude(S, ctx, M):  # noqa: F811
+    """Frames scaled by a power of two (R from 2^-95 to 2^115): every step of the iteration is the same, so the
+    results are, bit for bit, also in bins that take many steps (sources close to the floor)."""
+    F, T, grid = 37, 40, synth.DirectionGrid(24, 2)
+    X, H = scene(F, M, T, grid, 0.4, M + 2, floor=0.4)
+    ref = single(S, ctx, X, H, grid)
+    assert np.all(ref["st"] == 0)
+    for k in (-47, -30, 30, 55):
+        g = single(S, ctx, (X * np.float32(2.0 ** k)).astype(np.complex64), H, grid)
+        for name in ref:
+            assert np.array_equal(g[name], ref[name]), (k, name)
