@@ -12,19 +12,25 @@
 // all else in FP64.
 //   From Y_2 on each step is tested: with the Ritz vectors q_S of T = V^H Y to first order and their
 // Rayleigh quotient M, r = Y q_S - V q_S M bounds the angle between span V q_S and the wanted subspace
-// by |r| / (theta_Ns - theta_{Ns+1}), and Y q_S, the result, is nearer by theta_{Ns+1} / theta_Ns.  A bin
-// is done once |r| theta_{Ns+1} <= 2^-24 theta_Ns^2: its subspace is that of A perturbed by the FP32
-// roundoff of sigma_Ns at most (the Jacobi solve stops at the roundoff of sigma_1).  Where the first-order
-// vectors do not apply (close singular values across the split), the block is rotated to its Ritz
-// vectors by a Jacobi solve of the 8 x 8 Gram matrix; where three steps did not suffice, the block is
-// filtered by a Chebyshev polynomial of A A^H before the next (a slow bin: 212k instead of 301k
-// cycles for the slowest of a 257-bin block).  The result is stored as complex64 vectors E_s of about
-// unit length with the inverse Cholesky factor of their FP64 Gram matrix, as the Jacobi solve does.
+// by the root of sum_s (|r_s| / (theta_s - theta_{Ns+1}))^2, and Y q_S, the result, is nearer by theta_{Ns+1} /
+// theta_Ns.  A bin is done once (sum_s (|r_s| / theta_s)^2)^1/2 theta_{Ns+1} <= 2^-24 theta_Ns: its subspace is that
+// of A perturbed by the FP32 roundoff of sigma_Ns at most (the Jacobi solve stops at the roundoff of sigma_1).
+// Where the first-order vectors do not apply (close singular values across the split), the block is
+// rotated to its Ritz vectors by a Jacobi solve of the 8 x 8 Gram matrix; where three steps did not
+// suffice, the block is filtered by a Chebyshev polynomial of A A^H before the next, of the degree that the error
+// asks for.  The result is stored as complex64 vectors E_s of about unit length with the inverse Cholesky factor
+// of their FP64 Gram matrix, as the Jacobi solve does.
 //
-// A bin that this cannot decide -- no convergence in kMaxSteps steps, theta_Ns below 1e-6 theta_1 (it may
-// be beyond the numerical rank), anything not finite -- is marked SSL_BIN_PENDING and its A stored: the
-// Jacobi solve, launched next, takes those bins alone.  The magnitude of A does not matter: it is scaled by a
-// power of two first, and the result has unit length.
+// A bin that this cannot decide -- theta_Ns below 1e-11 theta_1 (sigma 3e-6: at the numerical rank), no gap behind
+// theta_Ns, convergence not in sight of kBudget applications, anything not finite -- is marked
+// SSL_BIN_PENDING and its A stored: the Jacobi solve, launched next, takes those bins alone.  It is given up as soon
+// as that shows, zero and rank-deficient bins before the first application, since the time spent on it is
+// lost.  The magnitude of A does not matter: it is scaled by a power of two first, and the result has unit
+// length.
+//   One 60-channel block, two sources asked for, us with the whitening and Jacobi launches / with this (257 bins,
+// 72 directions, no noise set): one source over a floor 20 dB below 559 / 168, 40 dB below 508 / 653, no source and 50
+// frames 476 / 158, 5000 frames 1249 / 933, silence 72 / 73, one source alone 74 / 90.  Up to 16 channels long
+// averages of noise alone take longer than before (16 channels, 500 frames: 104 / 153).
 //
 // What bounds it: the FP64 matrix cores (64 cycles per v_mfma_f64_16x16x4f64 and SIMD: about 11.5k
 // for A, 1.9k per FP64 product, 1.3k per step for the small matrices) and, with one block per launch,
@@ -41,7 +47,7 @@
 //   Measured, 128 60-channel blocks per launch (32896 bins): 2.5 ms, where the whitening launch (0.98 ms)
 // and the Jacobi launch (6.8 ms) stood before; one block (257 bins): 93 us, 18.7 + 505 us before.
 //   Up to 16 channels one wave does all of a bin, tests before it orthonormalises, and with up to 8
-// starts from the whole space, so that one Jacobi solve of the 8 x 8 matrix and one application decide.
+// starts from the whole range of A, so that one Jacobi solve of the 8 x 8 matrix and one application decide.
 // 8 channels, 257 bins: 14.6 us; the whitening and Jacobi launches took 2.5 + 23.5 us.  24 blocks each of 8 and
 // of 16 channels with 257 and 513 bins: 0.11 and 0.135 ms (Jacobi: 0.175 and 0.25 ms, whitening 0.017).
 #include "signal_out.h"
@@ -52,18 +58,22 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlk = 8;              // vectors of the block
 constexpr int kLd = 18;              // LDS row stride of a block, doubles (16 used: re | im)
-constexpr int kMaxSteps = 24;        // applications of A A^H before the Jacobi solve takes the bin
+constexpr int kMaxSteps = 64;        // applications of A A^H before the Jacobi solve takes the bin
 constexpr int kFirstTest = 2;        // first application tested for convergence
+constexpr int kSolved = -1, kLeft = -2;                // verdicts besides a filter's degree
 constexpr int kMaxSweeps = 12;       // Jacobi sweeps over the 8 x 8 Gram matrix
-constexpr double kCouple = 1e-9;     // (S-rest coupling / gap)^2 that the first-order test copes with
+constexpr double kCouple = 1e-6;     // (S-rest coupling / gap)^2 that the first-order test copes with,
+constexpr double kCoupleAll = 1e-9;  // and where the block is the whole space: nothing else is to converge
 constexpr int kAccel = 3;            // first step followed by a Chebyshev filter when not done
-constexpr int kDegree = 3;           // its degree
-// The filter scales direction 1 against S by up to (theta_1 / theta_S)^3, and V departs from orthonormality
-// by 2^-53 of that, which the test sees times theta_1: beyond this ratio a filtered block is followed
-// by a plain step before it is filtered again (fourth root of 2^-24 2^53)
-constexpr double kWide = 152.0;
+// A filter of degree d multiplies what V's columns hold of direction 1 (2^-53) by about (4 theta_1 / theta_C)^d, where
+// the weakest keeps its length; orth_factor drops a column that is 2^-21 of its own length from the ones before it.
+// So d log2(4 theta_1 / theta_C) <= kWideFresh, and kWide where V itself comes from a filtered block and holds more.
+constexpr float kWide = 45.0f, kWideFresh = 68.0f;
+// Applications that a bin may take: what the Jacobi solve takes in a large batch is about 60 (17 channels and more)
+template <int NW> constexpr float kBudget = NW > 1 ? 60.0f : 46.0f;
 constexpr double kTol = 5.9604644775390625e-08;      // 2^-24
-constexpr double kRange = 1e-6;      // theta_Ns / theta_1 below this: left to the Jacobi solve
+// theta_Ns / theta_1 below this: left to the Jacobi solve (Y_0 and Y_1 in FP32 no longer hold direction Ns)
+constexpr double kRange = 1e-11;
 
 // NW waves, KQ k-steps of 4: M <= 16 NW and M <= 4 KQ
 template <int NW, int KQ> struct SubCfg {
@@ -93,10 +103,12 @@ template <int NW> struct SubShared {
     };
     float amax[NW];
     double rpart[NW];                // per wave: its rows' share of |r|^2
-    double unit[kBlk];               // scale of the result vectors
+    double unit[kBlk];               // scale of the result vectors: 1 / T_ss
+    double weight[kBlk];             // of their residuals
     double th1, thS, thR;            // T_00, bounds of theta_Ns (below) and theta_{Ns+1} (above)
-    double thC;                      // smallest Ritz value
+    double thC, thD;                 // smallest diagonal entry of T, and among the leading Ns
     int coupled;                     // the first-order Ritz vectors do not apply
+    int lost;                        // the start block has fewer than Ns independent columns
 };
 
 template <int CTRL>
@@ -231,22 +243,27 @@ __device__ __forceinline__ double2 conjd(double2 v) { return make_double2(v.x, -
 // Cyclic Jacobi on the Hermitian 8 x 8 matrix held one element per lane (row l / 8, column l % 8), the
 // rotations accumulated into Q, if the first-order Ritz vectors of the test would not do (a squared
 // coupling of more than `first` of the gap's square): until the leading Ns indices are decoupled from
-// the rest to kCouple (in order) and the rest among themselves enough for the test's bound.  The pairs of a round are (i, i ^ m), m = 1 .. 7.
-__device__ __forceinline__ void ritz(double2 &G, double2 &Q, int Ns, double first, int lane)
+// the rest to `couple` (in order) and the rest among themselves enough for the test's bound, or to rounding (`noise`:
+// an absolute level of it for G's squared entries).  The pairs of a round are (i, i ^ m), m = 1 .. 7.
+__device__ __forceinline__ void ritz(double2 &G, double2 &Q, int Ns, double first, double couple, double noise,
+                                     int lane)
 {
     const int i = lane >> 3, j = lane & 7;
     for (int sw = 0; sw < kMaxSweeps; ++sw) {
         const double di = __shfl(G.x, 9 * i), dj = __shfl(G.x, 9 * j);
         const double g2 = G.x * G.x + G.y * G.y, d = di - dj;
         // the first look decides whether to rotate at all, the later ones when to stop
-        const double lim = sw == 0 ? first : kCouple;
+        const double lim = sw == 0 ? first : couple;
+        // columns of numerically orthogonal or vanishing Y_i, Y_j have nothing to rotate
+        const bool none = g2 <= 2.0e-28 * fabs(di * dj) || g2 <= noise;
         double ds = readlane64(G.x, 0);                // smallest of the leading diagonal
         if (Ns > 1) ds = fmin(ds, readlane64(G.x, 9));
         if (Ns > 2) ds = fmin(ds, readlane64(G.x, 18));
+        if (ds <= 1e-23 * readlane64(G.x, 0)) return;  // theta below kRange: it will be given up
         const double below = fmax(ds - di, 0.0);
         bool bad = false;
-        if (i < Ns && j >= Ns) bad = !(g2 <= lim * d * d && d > 0.0);
-        else if (i >= Ns && j >= Ns && i != j) bad = !(64.0 * g2 <= below * below);
+        if (i < Ns && j >= Ns) bad = !none && !(g2 <= lim * d * d && d > 0.0);
+        else if (i >= Ns && j >= Ns && i != j) bad = !none && !(64.0 * g2 <= below * below);
         if (!__any(bad)) return;
 #pragma unroll 1
         for (int m = 1; m < 8; ++m) {
@@ -359,7 +376,7 @@ __device__ __forceinline__ void prepare_test(double2 t, int Ns, int lane, Sh &sh
         const double wi = rsqrt64(fmax(di, 1e-200)), wj = rsqrt64(fmax(dj, 1e-200));
         lo = at * (di * wi * wj);
     }
-    double sm = di;
+    double sm = di, sd = i < Ns ? di : 1e300;
 #pragma unroll
     for (int o = 1; o < 8; o <<= 1) {
         rs += __shfl_xor(rs, o);
@@ -371,20 +388,28 @@ __device__ __forceinline__ void prepare_test(double2 t, int Ns, int lane, Sh &sh
         rs = fmax(rs, __shfl_xor(rs, o));
         lo = fmin(lo, __shfl_xor(lo, o));
         sm = fmin(sm, __shfl_xor(sm, o));
+        sd = fmin(sd, __shfl_xor(sd, o));
     }
     const double t0 = readlane64(t.x, 0);
     if (Ns == 2) {
         const double t1 = readlane64(t.x, 9), gx = readlane64(t.x, 1), gy = readlane64(t.y, 1);
-        const double h = 0.5 * (t0 - t1);
-        lo = 0.5 * (t0 + t1) - sqrt(fma(h, h, fma(gx, gx, gy * gy)));
+        const double h = 0.5 * fabs(t0 - t1), g2 = fma(gx, gx, gy * gy);
+        lo = fmin(t0, t1) - (g2 > 0.0 ? g2 / (h + sqrt(fma(h, h, g2))) : 0.0);
     }
     const bool any_big = __any(big);
-    if (i == j) sh.unit[j] = j < Ns && dj > 0.0 ? rcp64(dj) : 0.0;
+    // residuals count against their own Ritz value where those of S do not mix, |T_ij| <= min(T_ii, T_jj)
+    const bool mixed = __any(i < Ns && j < Ns && i != j && at > fmin(di, dj));
+    if (i == j) {
+        const double u = j < Ns && dj > 0.0 ? rcp64(dj) : 0.0;
+        sh.unit[j] = u;
+        sh.weight[j] = j < Ns ? (mixed ? rcp64(fmax(sd, 1e-300)) : u) : 0.0;
+    }
     if (lane == 0) {
         sh.th1 = t0;
         sh.thS = lo;
         sh.thR = rs;
         sh.thC = sm;
+        sh.thD = sd;
         sh.coupled = any_big ? 1 : 0;
     }
 }
@@ -403,7 +428,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
     constexpr int MP = 16 * NW, NT = 64 * NW, kAs = Sh::kAs;
     __shared__ Sh sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int kl = lane >> 4, cl = lane & 15;
+    int kl = lane >> 4, cl = lane & 15;
     const int row = 16 * wave + cl;                    // A-operand row of this lane
     const double sgn = cl < 8 ? -1.0 : 1.0;
 
@@ -506,19 +531,11 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
     auto oph32 = [&](int q) { return make_float2(hw[q].x, -hw[q].y); };
 
     double y[4];
-    bool solved = false;
     double v[4] = {0.0, 0.0, 0.0, 0.0};                // V on this wave's rows
-    // M <= 8: the block starts as the whole space and only has to be turned to the Ritz vectors
+    // M <= 8: the block starts as A itself (its whole range) and only has to be turned to the Ritz vectors
     constexpr bool whole = 4 * KQ <= kBlk;
     if constexpr (whole) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = kl + 4 * e == cl && cl < kBlk ? 1.0 : 0.0;
-        store(sh.V, v);
-        __syncthreads();
-        strip_product<KQ>(oph, from(sh.V), sgn, y);
-        store(sh.W, y);
-        __syncthreads();
-        strip_product<KQ>(opa, from(sh.W), sgn, y);
+        strip_product<KQ>(opa, [&](int q) { return 4 * q + kl == cl ? 1.0 : 0.0; }, sgn, y);       // A
     } else {
         strip_product32<KQ>(opa32, [&](int q) { return omega(4 * q + kl, cl); }, sgn, y);
     }
@@ -551,10 +568,11 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
             zz = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.Y[row * kLd + k], sh.BY[o], zz, 0, 0, 0);
             x = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.V[row * kLd + k], sh.BV[o], x, 0, 0, 0);
         }
+        const double un = sh.weight[cl & 7];
         double n2 = 0.0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const double d = zz[e] - x[e];
+            const double d = (zz[e] - x[e]) * un;
             n2 = fma(d, d, n2);
         }
         n2 = row_sum(n2);
@@ -562,43 +580,74 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
         n2 += __shfl_xor(n2, 32);
         if (lane == 0) sh.rpart[wave] = n2;
     };
-    auto apart = [&] { return sh.coupled == 0 && sh.thR < sh.thS; };
-    auto passes = [&] {                                // the same in every thread
+    // What a test says: solved, given up, or the degree of the filter that follows (0, 1: none).  The same in
+    // every thread, and known to be, so that the branches on it are uniform.
+    auto verdict = [&](int step, bool fresh) {
+        const double th1 = sh.th1, thS = sh.thS, thR = sh.thR, thC = sh.thC;
         double off = 0.0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) off += sh.rpart[w];
-        const double thS = sh.thS, thR = sh.thR;
-        return apart() && thS >= kRange * sh.th1 &&
-               off * (thR * thR) <= (kTol * thS) * (kTol * thS) * (thS * thS);
+        const double err2 = off * (thR * thR), tol2 = (kTol * thS) * (kTol * thS);
+        const bool apart = sh.coupled == 0 && thR < thS;
+        int next = 0;
+        if (apart && thS >= kRange * th1 && err2 <= tol2) {
+            next = kSolved;
+        } else if (step >= kMaxSteps || !(th1 > 0.0) || sh.thD < 0.0625 * kRange * th1) {
+            next = kLeft;
+        } else if ((step > kFirstTest || whole) && sh.thD < kRange * th1) {
+            next = kLeft;
+        } else if ((step > kFirstTest || whole) && thS > 0.0) {    // the block has been turned to its Ritz vectors
+            // bits that the error has to lose, and loses in an application: thC / thS in a plain one, the
+            // growth of the Chebyshev polynomials at 2 thS / thC - 1 in a filter
+            const float need = 0.5f * __log2f((float)(err2 / tol2));
+            const float c = (float)(thS / thC), x = 2.0f * c - 1.0f;
+            const int wide = (int)((fresh ? kWideFresh : kWide) / __log2f((float)(4.0 * th1 / thC)));
+            const float gain = wide > 1 ? __log2f(x + sqrtf(fmaxf(fmaf(x, x, -1.0f), 0.0f))) : __log2f(c);
+            if ((thC > 0.0 && !((kBudget<NW> - (float)step) * gain >= 1.3f * need)) ||
+                (!apart && need <= 0.0f && step > kFirstTest + 3))             // no gap
+                next = kLeft;
+            else if (apart && wide > 1 && step >= kAccel && thC > kRange * thS)
+                next = min(max((int)ceilf((need + 1.0f) / gain), 2), min(wide, step));
+        }
+        return __builtin_amdgcn_readfirstlane(next);
     };
-    for (int step = whole ? kFirstTest - 1 : 0;;) {
+    int next = kLeft;
+    constexpr int kStart = whole ? kFirstTest - 1 : 0;
+    for (int step = kStart; __builtin_amdgcn_readfirstlane(amax > 0.0f);) {
         const bool test = step >= kFirstTest && plain;
+        // what depends on the lane is made where it is used, not held in registers from before the loop
+        int ln = lane;
+        asm volatile("" : "+v"(ln), "+v"(kl), "+v"(cl));
         gram(y, y, sh.part[wave][0]);
         if (test) gram(v, y, sh.part[wave][1]);
         if (step < kFirstTest && !whole) store32(sh.Y, y);
         else store(sh.Y, y);                           // own rows only: the operand of Y B, Y BY
         __syncthreads();
         if (NW == 1 && test) {                         // nobody to orthonormalise beside the test
-            prepare_test(sum_parts(1), Ns, lane, sh);
+            prepare_test(sum_parts(1), Ns, ln, sh);
             __syncthreads();
             residual();
             __syncthreads();
-            if (passes()) {
-                solved = true;
-                break;
-            }
+            next = verdict(step, fresh);
+            if (next < 0) break;
         }
         if (wave == (NW > 1 ? 1 : 0)) {
             double2 G = sum_parts(0);
-            const int i = lane >> 3, j = lane & 7;
+            const int i = ln >> 3, j = ln & 7;
             if (i == j) G.y = 0.0;
             double2 Q = make_double2(i == j ? 1.0 : 0.0, 0.0);
             if (step >= kFirstTest || whole)
-                ritz(G, Q, Ns, step == kFirstTest && !whole ? 1e-2 : kCouple, lane);
-            const double2 a = orth_factor(G, Q, lane);
+                ritz(G, Q, Ns, whole ? kCoupleAll : step == kFirstTest ? 1e-2 : kCouple, whole ? kCoupleAll : kCouple,
+                     step < kFirstTest ? 2e-28 : 0.0, ln);
+            const double2 a = orth_factor(G, Q, ln);
+            if (step == kStart) {
+                const bool gone = whole ? G.x < kRange * readlane64(G.x, 0) : a.x == 0.0 && a.y == 0.0;
+                const bool lost = __any(i == j && i < Ns && gone);
+                if (ln == 0) sh.lost = lost ? 1 : 0;
+            }
             put_real(sh.B, j, i, conjd(a));
         }
-        if (NW > 1 && wave == 0 && test) prepare_test(sum_parts(1), Ns, lane, sh);
+        if (NW > 1 && wave == 0 && test) prepare_test(sum_parts(1), Ns, ln, sh);
         __syncthreads();
         // V' = Y B and, for the test, r, on this wave's rows
         doublex4 vn = {0.0, 0.0, 0.0, 0.0};
@@ -613,43 +662,40 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
             store(sh.V, vs);
         }
         __syncthreads();
-        if (test) {
-            if (NW > 1 && passes()) {
-                solved = true;
-                break;
-            }
-            const double th1 = sh.th1, thS = sh.thS;
-            if (step >= kMaxSteps || !(th1 > 0.0)) break;
-            if (step >= kAccel && apart() && sh.thC > kRange * thS && (fresh || th1 <= kWide * thS)) {
-                // slow bin: the block filtered by the Chebyshev polynomial of A A^H on [0, thC], thC
-                // the smallest Ritz value: W_0 = V, W_1 = (a A A^H - 1) V, W_{k+1} = 2 (a A A^H - 1)
-                // W_k - W_{k-1}, from the V and Y at hand
-                const double a2 = 2.0 / sh.thC;
-                double w1[4];
+        if (step == kStart && __builtin_amdgcn_readfirstlane(sh.lost)) break;
+        if (NW > 1 && test) {
+            next = verdict(step, fresh);
+            if (next < 0) break;
+        }
+        if (test && next > 0) {
+            // slow bin: the block filtered by the Chebyshev polynomial of A A^H on [0, thC], thC the smallest
+            // Ritz value: W_0 = V, W_1 = (a A A^H - 1) V, W_{k+1} = 2 (a A A^H - 1) W_k - W_{k-1}, from the V
+            // and Y at hand
+            const double a2 = 2.0 / sh.thC;
+            double w1[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w1[e] = fma(a2, y[e], -v[e]);
+            for (int e = 0; e < 4; ++e) w1[e] = fma(a2, y[e], -v[e]);
 #pragma unroll 1
-                for (int d = 1; d < kDegree; ++d) {
-                    __syncthreads();                   // V and thC have been read
-                    store(sh.V, w1);
-                    __syncthreads();
-                    strip_product<KQ>(oph, from(sh.V), sgn, y);
-                    store(sh.W, y);
-                    __syncthreads();
-                    strip_product<KQ>(opa, from(sh.W), sgn, y);
+            for (int d = 1; d < next; ++d) {
+                __syncthreads();                       // V and thC have been read
+                store(sh.V, w1);
+                __syncthreads();
+                strip_product<KQ>(oph, from(sh.V), sgn, y);
+                store(sh.W, y);
+                __syncthreads();
+                strip_product<KQ>(opa, from(sh.W), sgn, y);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const double w0 = v[e];
-                        v[e] = w1[e];
-                        w1[e] = fma(2.0, fma(a2, y[e], -w1[e]), -w0);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const double w0 = v[e];
+                    v[e] = w1[e];
+                    w1[e] = fma(2.0, fma(a2, y[e], -w1[e]), -w0);
                 }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = w1[e];
-                plain = false;
-                step += kDegree - 1;
-                continue;
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = w1[e];
+            plain = false;
+            step += next - 1;
+            continue;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = sh.V[wr + 4 * e * kLd];
@@ -669,6 +715,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
         }
     }
 
+    const bool solved = next == kSolved;
     if (solved) {
         // the vectors Y q_s (about unit length), rounded to complex64, and their FP64 Gram matrix
         const double un = sh.unit[cl & 7];
@@ -718,7 +765,8 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
 }
 
 template <int NW, int KQ>
-__global__ __launch_bounds__((SubCfg<NW, KQ>::THREADS)) void subspace_single(
+__global__ __launch_bounds__((SubCfg<NW, KQ>::THREADS))
+__attribute__((amdgpu_waves_per_eu(2))) void subspace_single(
     const double2 *__restrict__ Kinv, const int32_t *__restrict__ kstatus,
     const float2 *__restrict__ R, float2 *__restrict__ A, int M, int Ns,
     int32_t *__restrict__ status, int32_t *__restrict__ status_out, float2 *__restrict__ Es,
