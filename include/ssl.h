@@ -342,7 +342,8 @@ typedef struct {
     int32_t *conv;             /* [F][3] out or NULL: per bin the Jacobi solve's sweeps,
                                   rotations and numerical rank (as ssl_gsvd's conv; where the
                                   signal vectors come from the subspace iteration, the Jacobi
-                                  solve runs besides for these numbers alone) */
+                                  solve runs besides for these numbers alone, so that asking for
+                                  them costs its time and leaves the results as they are) */
 } ssl_block_desc;
 
 /* Whole path (as ssl_localize) for nblocks blocks of possibly different shapes, in one set of

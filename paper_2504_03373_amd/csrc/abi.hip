@@ -1135,7 +1135,9 @@ ssl_status ssl_sliding_localize(ssl_sliding s, ssl_noise K, const void *H, ssl_p
 namespace {
 
 constexpr int kIterClass = 1000;     // offset of the subspace iteration's classes in the item lists
-constexpr int kJacobiQueues = 4;     // counters[0..3]: work queues of Jacobi classes 8/16/32/64
+constexpr int kJacobiQueues = 4;     // counters[0..3]: work queues of Jacobi classes 8/16/32/64,
+                                     // then the lists of bins left to them
+constexpr int kCounters = kJacobiQueues * (1 + kLeftLists * kLeftStride);
 
 int jacobi_queue(int cls) { return cls == 8 ? 0 : cls == 16 ? 1 : cls == 32 ? 2 : 3; }
 
@@ -1154,6 +1156,7 @@ struct Plan {
     // over the same items, by Jacobi class, for the bins it leaves
     std::vector<Seg> iter, pending;
     int nblocks = 0, n_items = 0, max_dc = 0, max_fc = 0;
+    int n_whiten = 0;                      // whitening items: behind them, the lists of bins left (device only)
     std::vector<Seg> gevd;                 // (block, bin) items of GEVD-MUSIC blocks, by class; the
                                            // first `extra` of a class form noise vectors
 };
@@ -1318,13 +1321,17 @@ hipError_t enqueue_batch(ssl_ctx ctx, const Plan &P, const BlockDev *blk, const 
         if (e != hipSuccess) return e;
     }
     for (const Seg &s : P.pending) {
+        // every whitening item belongs to a block that is not solved by iteration: there is room for all of these
+        const LeftBins left{const_cast<int2 *>(l_wh) + P.n_whiten + (s.start - P.pending.front().start),
+                            ctx->counters + kJacobiQueues + kLeftLists * kLeftStride * jacobi_queue(s.cls), s.count};
         e = timed(ctx, SSL_K_JACOBI, st, [&] {
             for (const Seg &i : P.iter) {
                 if (i.start < s.start || i.start >= s.start + s.count) continue;
-                const hipError_t le = launch_subspace_batch(blk, l_jac + i.start, i.count, i.cls, st);
+                const hipError_t le = launch_subspace_batch(blk, l_jac + i.start, i.count, i.cls, left,
+                                                            i.start - s.start, st);
                 if (le != hipSuccess) return le;
             }
-            return launch_jacobi_pending(blk, l_jac + s.start, s.count, s.cls,
+            return launch_jacobi_pending(blk, left, s.cls,
                                          ctx->jac_lanes[jacobi_class_index(s.cls)],
                                          SSL_DEFAULT_SWEEPS, s.extra, sub_full_for(ctx, 2, true),
                                          st);
@@ -1352,7 +1359,8 @@ hipError_t enqueue_batch(ssl_ctx ctx, const Plan &P, const BlockDev *blk, const 
         if (e != hipSuccess) return e;
     }
     return timed(ctx, SSL_K_BINSUM, st, [&] {
-        return launch_binsum_batch(blk, P.nblocks, P.max_dc, P.max_fc, st);
+        return launch_binsum_batch(blk, P.nblocks, P.max_dc, P.max_fc, ctx->counters + kJacobiQueues,
+                                   kCounters - kJacobiQueues, st);
     });
 }
 
@@ -1773,7 +1781,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
     const size_t tail_bytes = 2 * (sizeof(int2) + sizeof(int)) * (size_t)nblocks;
     const size_t list_bytes = sizeof(int2) * 5 * (size_t)n_items + tail_bytes;
     if ((s = ws_reserve(ctx, ws_total)) != SSL_OK) return s;
-    if ((s = counters_reserve(ctx, kJacobiQueues)) != SSL_OK) return s;
+    if ((s = counters_reserve(ctx, kCounters)) != SSL_OK) return s;
     if ((s = bdesc_reserve(ctx, desc_bytes + list_bytes)) != SSL_OK) return s;
 
     // the previous call's staging copy must have completed before the buffer is rewritten
@@ -1919,6 +1927,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
             sg.count = pos - sg.start;
             plan.whiten.push_back(sg);
         }
+        plan.n_whiten = pos;
     }
     {
         // Jacobi items by class, then those of the subspace iteration by its classes, which are finer:

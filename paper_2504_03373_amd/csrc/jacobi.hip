@@ -1306,7 +1306,7 @@ __device__ __forceinline__ void jacobi_bin(float2 *__restrict__ Af, int kst, int
         // FP32 sums would lose sigma_1 / sigma_s times the rounding of the result.  Each vector
         // is normalised in FP32 (Lf below makes the projector exact); they go to diag, vhead,
         // diag1, free by now.
-        if (sig_only) {
+        if (sig_only && Esf != nullptr) {               // (null: statistics only)
             __syncthreads();                            // perm is complete
             auto sv = [&](int k) -> float2 * { return k == 0 ? diag : (k == 1 ? vhead : diag1); };
             const float sc = ldexpf(1.0f, -ex);
@@ -1440,47 +1440,35 @@ __attribute__((amdgpu_waves_per_eu(JacobiCfg<MP, G>::WAVES_PER_EU))) void jacobi
     }
 }
 
-// After the subspace iteration over the same items: solves the bins it left (status
-// SSL_BIN_PENDING), and runs the solve of the others of a block that asks for the Jacobi statistics
-// (conv) for those alone.  Workgroup w looks at the items w, w + grid, .. (one per lane of wave 0,
-// 64 at a time) and takes the ones to be solved in turn; few are, so most workgroups only look.
+// After the subspace iteration: the lists of bins it left, a list by every kLeftLists-th workgroup, drawn one by
+// one as above (the first by each workgroup without a draw, so that a launch with nothing to do reads one
+// number).  Solves the bins that have no signal vectors yet (status SSL_BIN_PENDING); the
+// others belong to blocks that ask for the Jacobi statistics (conv) and are run for those alone.  A later kernel
+// of the batch clears the queue.
 template <int MP, int G>
 __global__ __launch_bounds__((JacobiCfg<MP, G>::THREADS))
 __attribute__((amdgpu_waves_per_eu(JacobiCfg<MP, G>::WAVES_PER_EU))) void jacobi_pending(
-    const BlockDev *__restrict__ blk, const int2 *__restrict__ items, int n_items,
-    int max_sweeps, int sub_full)
+    const BlockDev *__restrict__ blk, LeftBins left, int max_sweeps, int sub_full)
 {
-    __shared__ unsigned long long todo_s;
-    const int tid = threadIdx.x, w = blockIdx.x, nw = gridDim.x;
-    const int mine = (n_items - w + nw - 1) / nw;               // items of this workgroup
-    for (int base = 0; base < mine; base += 64) {
+    __shared__ unsigned int item_s;
+    const int l = blockIdx.x % kLeftLists;
+    unsigned int *queue = left.queue + kLeftStride * l;          // entries, tickets
+    const unsigned int n = gload(queue), mine = (gridDim.x - l + kLeftLists - 1) / kLeftLists;
+    for (unsigned int i = blockIdx.x / kLeftLists; i < n;) {     // uniform
+        const int2 it = left.list(l)[i];
+        const BlockDev &B = blk[it.x];
+        const int f = it.y, M = B.M, Ns = B.Ns;
+        const bool stats = B.status[f] != SSL_BIN_PENDING;       // solved: statistics only
+        jacobi_bin<MP, G>(B.A + (size_t)f * M * M, B.kstatus ? B.kstatus[f] : SSL_BIN_OK, M, Ns, max_sweeps,
+                          nullptr, nullptr, stats ? nullptr : B.status + f,
+                          B.conv ? B.conv + 3 * (size_t)f : nullptr, nullptr, sub_full,
+                          stats ? nullptr : B.Es + (size_t)f * Ns * M,
+                          stats ? nullptr : B.Esl + 6 * (size_t)f,
+                          !stats && B.status_out ? B.status_out + f : nullptr);
+        if (threadIdx.x == 0) item_s = mine + atomicAdd(queue + 1, 1u);
         __syncthreads();
-        if (tid < 64) {
-            bool need = false;
-            if (base + tid < mine) {
-                const int2 it = items[w + (size_t)(base + tid) * nw];
-                const BlockDev &B = blk[it.x];
-                need = B.conv != nullptr || B.status[it.y] == SSL_BIN_PENDING;
-            }
-            const unsigned long long m = __ballot(need);
-            if (tid == 0) todo_s = m;
-        }
+        i = item_s;
         __syncthreads();
-        unsigned long long todo = todo_s;
-        while (todo) {                                           // uniform
-            const int b = __ffsll(todo) - 1;
-            todo &= todo - 1;
-            const int2 it = items[w + (size_t)(base + b) * nw];
-            const BlockDev &B = blk[it.x];
-            const int f = it.y, M = B.M, Ns = B.Ns;
-            const bool stats = B.status[f] != SSL_BIN_PENDING;  // solved: statistics only
-            jacobi_bin<MP, G>(B.A + (size_t)f * M * M, B.kstatus ? B.kstatus[f] : SSL_BIN_OK, M,
-                              Ns, max_sweeps, nullptr, nullptr, stats ? nullptr : B.status + f,
-                              B.conv ? B.conv + 3 * (size_t)f : nullptr, nullptr, sub_full,
-                              stats ? nullptr : B.Es + (size_t)f * Ns * M,
-                              stats ? nullptr : B.Esl + 6 * (size_t)f,
-                              !stats && B.status_out ? B.status_out + f : nullptr);
-        }
     }
 }
 
@@ -1748,11 +1736,11 @@ hipError_t launch_cfg(ssl_c64 *A, const int32_t *kstatus, int F, int M, int Ns, 
 }
 
 template <int MP, int G>
-hipError_t launch_pending(const BlockDev *blk, const int2 *items, int n_items, int max_sweeps,
+hipError_t launch_pending(const BlockDev *blk, const LeftBins &left, int max_sweeps,
                           int grid, int sub_full, hipStream_t st)
 {
     hipLaunchKernelGGL((jacobi_pending<MP, G>), dim3(grid), dim3(JacobiCfg<MP, G>::THREADS), 0, st,
-                       blk, items, n_items, max_sweeps, sub_full);
+                       blk, left, max_sweeps, sub_full);
     return hipGetLastError();
 }
 
@@ -1836,14 +1824,14 @@ hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int N
     return e;
 }
 
-hipError_t launch_jacobi_pending(const BlockDev *blk, const int2 *items, int n_items, int cls,
+hipError_t launch_jacobi_pending(const BlockDev *blk, const LeftBins &left, int cls,
                                  int lanes, int max_sweeps, int grid, int sub_full,
                                  hipStream_t st)
 {
-    if (n_items <= 0) return hipSuccess;
+    if (grid <= 0) return hipSuccess;
     hipError_t e = hipErrorInvalidValue;
     dispatch(cls, lanes, [&]<int MP, int G>() {
-        e = launch_pending<MP, G>(blk, items, n_items, max_sweeps, grid, sub_full, st);
+        e = launch_pending<MP, G>(blk, left, max_sweeps, grid, sub_full, st);
     });
     return e;
 }

@@ -194,8 +194,10 @@ __global__ __launch_bounds__(kThreads) void binsum_part_batch(const BlockDev *__
     binsum_part_body(B.P, B.F, B.D, B.part, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(kFinal) void binsum_final_batch(const BlockDev *__restrict__ blk)
+__global__ __launch_bounds__(kFinal) void binsum_final_batch(const BlockDev *__restrict__ blk,
+                                                             unsigned int *__restrict__ clear, int n_clear)
 {
+    if (blockIdx.x == 0 && (int)threadIdx.x < n_clear) clear[threadIdx.x] = 0u;
     const BlockDev &B = blk[blockIdx.x];
     const int nch = (B.F + SSL_BINSUM_CHUNK - 1) / SSL_BINSUM_CHUNK;
     binsum_final_body(B.part, nch, B.D, B.Pbar, B.n_az, B.n_el, B.Ns, B.peaks, B.peak_val);
@@ -235,14 +237,14 @@ hipError_t launch_binsum_peaks(const float *P, int F, int D, float *Pbar, float 
 int binsum_threads() { return kThreads; }
 
 hipError_t launch_binsum_batch(const BlockDev *blk, int nblocks, int max_dchunks, int max_fchunks,
-                               hipStream_t st)
+                               unsigned int *clear, int n_clear, hipStream_t st)
 {
     if (nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(binsum_part_batch, dim3(max_dchunks, max_fchunks, nblocks),
                        dim3(kThreads), 0, st, blk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(binsum_final_batch, dim3(nblocks), dim3(kFinal), 0, st, blk);
+    hipLaunchKernelGGL(binsum_final_batch, dim3(nblocks), dim3(kFinal), 0, st, blk, clear, n_clear);
     return hipGetLastError();
 }
 

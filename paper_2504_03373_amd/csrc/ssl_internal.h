@@ -208,8 +208,9 @@ hipError_t launch_steer_gevd_batch(const BlockDev *blk, const int2 *items, int n
 hipError_t launch_steer_batch(const BlockDev *blk, const int2 *items, int n_items,
                               const int2 *groups, const int *gblocks, int cls, int waves,
                               int max_dtiles, ssl_prec hprec, hipStream_t st);
-hipError_t launch_binsum_batch(const BlockDev *blk, int nblocks, int max_dchunks,
-                               int max_fchunks, hipStream_t st);
+// (also clears n_clear counters, for the next batch)
+hipError_t launch_binsum_batch(const BlockDev *blk, int nblocks, int max_dchunks, int max_fchunks,
+                               unsigned int *clear, int n_clear, hipStream_t st);
 int jacobi_threads(int cls, int lanes);
 inline int jacobi_class_index(int cls) { return cls == 8 ? 0 : cls == 16 ? 1 : cls == 32 ? 2 : 3; }
 inline int steer_class_index(int cls) { return cls == 1 ? 0 : cls == 2 ? 1 : 2; }
@@ -269,17 +270,33 @@ hipError_t launch_jacobi(ssl_c64 *A, const int32_t *kstatus, int F, int M, int N
                          int32_t *bin_status, int32_t *conv, hipStream_t st,
                          ssl_c64 *U = nullptr, int sub_full = -1, ssl_c64 *Es = nullptr,
                          ssl_c128 *Esl = nullptr, bool pending = false, int32_t *status_out = nullptr);
+// The bins of a batch that the subspace iteration leaves to the Jacobi solve, per Jacobi class: kLeftLists lists
+// in one array of as many entries as the class has items (item i goes to list i mod kLeftLists, which has
+// room for every such i), so that workgroups ending together do not queue for one counter (one list: 24 blocks of
+// 16 channels, all bins left, 256 us instead of 151).
+constexpr int kLeftLists = 8, kLeftStride = 7;      // counters of a list: entries, tickets
+struct LeftBins {
+    int2 *items;
+    unsigned int *queue;
+    int count;                                      // items of the class
+    __host__ __device__ int2 *list(int l) const
+    {
+        const int per = count / kLeftLists, rest = count % kLeftLists;
+        return items + l * per + (l < rest ? l : rest);
+    }
+};
 // Signal vectors by block subspace iteration (subspace.hip, Ns <= 3): Es,
 // Esl and status SSL_BIN_OK, or status SSL_BIN_PENDING and A = K^{-1} R (A itself where Kinv is
 // null: R) for the Jacobi solve that has to follow -- launch_jacobi with pending, or
-// launch_jacobi_pending over the same items (whose blocks all have Es and p = 2).  bin_status is workspace;
+// launch_jacobi_pending over the items that the batched form lists (left: counters zero on entry; first: the
+// launch's first item within the class; blocks with Es and p = 2).  bin_status is workspace;
 // status_out (optional): the caller's copy of the final statuses.
 hipError_t launch_subspace(const ssl_c128 *Kinv, const int32_t *kstatus, const ssl_c64 *R,
                            ssl_c64 *A, int F, int M, int Ns, int32_t *bin_status,
                            int32_t *status_out, ssl_c64 *Es, ssl_c128 *Esl, hipStream_t st);
 hipError_t launch_subspace_batch(const BlockDev *blk, const int2 *items, int n_items, int cls,
-                                 hipStream_t st);
-hipError_t launch_jacobi_pending(const BlockDev *blk, const int2 *items, int n_items, int cls,
+                                 const LeftBins &left, int first, hipStream_t st);
+hipError_t launch_jacobi_pending(const BlockDev *blk, const LeftBins &left, int cls,
                                  int lanes, int max_sweeps, int grid, int sub_full,
                                  hipStream_t st);
 // Full sweeps before the subspace phase (p = 2): none.  The signal set is chosen on the column

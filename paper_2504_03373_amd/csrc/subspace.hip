@@ -416,9 +416,10 @@ __device__ __forceinline__ void prepare_test(double2 t, int Ns, int lane, Sh &sh
 
 // One bin.  Kf: K^{-1} of the bin ([M][M] FP64) or null (SEVD-MUSIC: A = R); Rf, Af: [M][M] complex64,
 // Af written only where the Jacobi solve will read it (never with Kf null: A is R there).  stf: the status
-// that the Jacobi solve looks at; outf: the caller's copy of a final one, or null.
+// that the Jacobi solve looks at; outf: the caller's copy of a final one, or null.  False where the Jacobi solve
+// has to follow.
 template <int NW, int KQ>
-__device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int kst,
+__device__ __forceinline__ bool subspace_bin(const double2 *__restrict__ Kf, int kst,
                                              const float2 *__restrict__ Rf, float2 *__restrict__ Af,
                                              int M, int Ns, bool keep_a, int32_t *__restrict__ stf,
                                              int32_t *__restrict__ outf,
@@ -435,7 +436,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
     if (kst != SSL_BIN_OK) {                           // uniform: the noise set failed in this bin
         if (tid == 0) gstore(stf, (int32_t)kst);
         if (tid == 0 && outf) gstore(outf, (int32_t)kst);
-        return;
+        return true;
     }
     {
         double2 kw[KQ];                                // this wave's rows of K^{-1}
@@ -762,6 +763,7 @@ __device__ __forceinline__ void subspace_bin(const double2 *__restrict__ Kf, int
                        make_float2(ldexpf(aw[q].x, ex), ldexpf(aw[q].y, ex)));
         }
     }
+    return solved;
 }
 
 template <int NW, int KQ>
@@ -779,20 +781,27 @@ __attribute__((amdgpu_waves_per_eu(2))) void subspace_single(
                          Es + (size_t)f * Ns * M, Esl + 6 * (size_t)f);
 }
 
-// Item = (block, bin).
+// Item = (block, bin).  Lists the items that the Jacobi launch takes: those not solved here, and those of blocks
+// that ask for the Jacobi statistics.
 template <int NW, int KQ>
 __global__ __launch_bounds__((SubCfg<NW, KQ>::THREADS))
 __attribute__((amdgpu_waves_per_eu(3))) void subspace_batch(
-    const BlockDev *__restrict__ blk, const int2 *__restrict__ items)
+    const BlockDev *__restrict__ blk, const int2 *__restrict__ items, LeftBins left, int first)
 {
     const int2 it = items[blockIdx.x];
     const BlockDev &B = blk[it.x];
     const int f = it.y, M = B.M, Ns = B.Ns;
     const size_t o = (size_t)f * M * M;
     const bool whiten = B.Kinv && !B.Kisq;             // GEVD: A = C = W R W is there already
-    subspace_bin<NW, KQ>(whiten ? B.Kinv + o : nullptr, B.kstatus ? B.kstatus[f] : SSL_BIN_OK,
-                         (B.Kisq ? B.A : B.R) + o, B.A + o, M, Ns, B.conv != nullptr, B.status + f,
-                         B.status_out ? B.status_out + f : nullptr, B.Es + (size_t)f * Ns * M, B.Esl + 6 * (size_t)f);
+    const bool stats = B.conv != nullptr;
+    const bool solved = subspace_bin<NW, KQ>(whiten ? B.Kinv + o : nullptr, B.kstatus ? B.kstatus[f] : SSL_BIN_OK,
+                                             (B.Kisq ? B.A : B.R) + o, B.A + o, M, Ns, stats, B.status + f,
+                                             B.status_out ? B.status_out + f : nullptr,
+                                             B.Es + (size_t)f * Ns * M, B.Esl + 6 * (size_t)f);
+    if (threadIdx.x == 0 && (!solved || stats)) {
+        const int l = (first + (int)blockIdx.x) % kLeftLists;
+        left.list(l)[atomicAdd(left.queue + kLeftStride * l, 1u)] = it;
+    }
 }
 
 // Calls fn.template operator()<NW, KQ>() for a subspace class.
@@ -827,12 +836,12 @@ hipError_t launch_subspace(const ssl_c128 *Kinv, const int32_t *kstatus, const s
 }
 
 hipError_t launch_subspace_batch(const BlockDev *blk, const int2 *items, int n_items, int cls,
-                                 hipStream_t st)
+                                 const LeftBins &left, int first, hipStream_t st)
 {
     if (n_items <= 0) return hipSuccess;
     return with_class(cls, [&]<int NW, int KQ>() {
         hipLaunchKernelGGL((subspace_batch<NW, KQ>), dim3(n_items), dim3(SubCfg<NW, KQ>::THREADS), 0,
-                           st, blk, items);
+                           st, blk, items, left, first);
         return hipGetLastError();
     });
 }

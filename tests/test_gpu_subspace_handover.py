@@ -82,3 +82,42 @@ def test_any_magnitude(S, ctx, M):  # noqa: F811
         g = single(S, ctx, (X * np.float32(2.0 ** k)).astype(np.complex64), H, grid)
         for name in ref:
             assert np.array_equal(g[name], ref[name]), (k, name)
+
+
+def test_lists_of_bins_left(S, ctx):  # noqa: F811
+    """Blocks of every Jacobi class in one batch, replayed on other data: all bins left to the Jacobi solve,
+    none, every other one, in blocks with and without the Jacobi statistics.  Every call equals its blocks'
+    single-block calls bit for bit and has the statistics of the first."""
+    import torch
+    F, T, grid = 41, 30, synth.DirectionGrid(24, 2)
+    cases = []
+    for M, stats in ((8, False), (16, True), (24, False), (60, True), (60, False), (12, False)):
+        hard, H = scene(F, M, T, grid, 0.0, M, floor=0.0)          # rank 1: no second direction
+        easy, _ = scene(F, M, T, grid, 0.7, M + 1)
+        mixed = easy.copy()
+        mixed[::2] = hard[::2]
+        cases.append(dict(data=[to_dev(x) for x in (hard, easy, mixed)], X=to_dev(easy), H=to_dev(H), o=outs(F, 48),
+                          cv=torch.zeros((F, 3), dtype=torch.int32, device="cuda:0") if stats else None))
+
+    def call():
+        S.ssl_localize_batch(ctx, [S.block_desc(c["X"], None, c["H"], grid.n_az, grid.n_el, 2, c["o"]["pk"],
+                                                c["o"]["pv"], c["o"]["Pbar"], c["o"]["st"], c["cv"]) for c in cases],
+                             S.SSL_FP32, 2)
+
+    seen = {}
+    for kind in (0, 1, 2, 1, 0, 2):
+        for c in cases:
+            c["X"].copy_(c["data"][kind])
+            if c["cv"] is not None:
+                c["cv"].fill_(-7)
+        call()
+        for n, c in enumerate(cases):
+            s = outs(F, 48)
+            S.ssl_localize(ctx, c["X"], None, c["H"], S.SSL_FP32, grid.n_az, grid.n_el, 2, 2, s["pk"], s["pv"],
+                           s["Pbar"], s["st"])
+            for k in s:
+                assert np.array_equal(to_host(s[k]), to_host(c["o"][k])), (kind, n, k)
+            if c["cv"] is not None:
+                cv = to_host(c["cv"])
+                assert np.all(cv >= 0)
+                assert np.array_equal(seen.setdefault((kind, n), cv), cv)
