@@ -435,7 +435,7 @@ int ssl_ctx_get_stop(ssl_ctx ctx);
  * decide.
  *   SSL_PROJ_SIGNAL   (default) this form wherever it applies: p = 2, the Jacobi backend,
  *                     1 <= Ns <= 3 (GEVD: with h replaced by K^{-1/2} h in the denominator, for two and
- *                     three sources and 30..32, 45..48 or 60 channels, where it is faster), any
+ *                     three sources and 30..32, 36..48 or 57..60 channels, where it is faster), any
  *                     table precision, in ssl_localize, ssl_localize_noalloc, ssl_localize_batch
  *                     (per block: a batch may mix blocks of both forms) and, without conv and under
  *                     a stop mode as above, ssl_sliding_localize;

@@ -156,18 +156,21 @@ hipError_t launch_svd(ssl_ctx ctx, ssl_c64 *A, const int32_t *kst, int F, int M,
 }
 // Whether eq.5 is evaluated through the signal subspace (FP64, steer_sig.hip): p = 2, the Jacobi
 // backend, Ns <= 3, any table precision, unless the context asks for the noise-vector projection.
-// GEVD-MUSIC (on K^{-1/2} h): only where that is no slower (to 4%) even when every block of a batch has a
-// noise set of its own and |K^{-1/2} h|^2 serves one block each -- a block's results do not depend on the
-// batch it is in, so the choice cannot -- which takes nearly full tiles of 16 rows (at most one row per
-// tile empty) and the longer Jacobi solves of two and three sources.  257 bins, 1368 directions, 8 blocks
-// of two sources, us with the noise-vector form / with this form on sets of their own / on one set: 17 channels 359
-// / 565 / 214, 32: 610 / 592 / 229, 33: 944 / 1171 / 403, 48: 1527 / 1217 / 437, 56: 1712 / 1767 / 567, 60: 1832 /
-// 1780 / 579, 64 (whose K^{-1/2} leaves LDS for one workgroup per CU): 1877 / 2411 / 713; 60 with one source 1745 / 1839
-// / 650.  One block: 60 channels 423 / 296, 32 channels 202 / 125.
+// GEVD-MUSIC (on K^{-1/2} h), two and three sources: where that is no slower even when every block of a batch has a
+// noise set of its own and |K^{-1/2} h|^2 serves one block each -- a block's results do not depend on the batch it
+// is in, so the choice cannot.  What it costs goes by tiles of 16 rows, so it depends on how many rows of them
+// are empty.  257 bins, 1368 directions, 8 blocks of two sources, us with the noise-vector form / with this form on sets
+// of their own / on one set: 24 channels 515 / 579 / 228, 29: 636 / 622 / 239, 30: 643 / 602 / 246, 32: 667 / 613 / 243;
+// 33: 966 / 1191 / 417, 36: 1265 / 1179 / 404, 40: 1324 / 1194 / 416, 45: 1530 / 1276 / 450, 48: 1578 / 1255 / 455; 49: 1702
+// / 1791 / 564, 54: 1769 / 1790 / 572, 56: 1799 / 1810 / 577, 57: 1878 / 1838 / 595, 58: 1901 / 1807 / 592, 59: 1922 / 1857 /
+// 602, 60: 1934 / 1812 / 593; 64 channels, whose K^{-1/2} leaves LDS for one workgroup per CU, 1877 / 2411 / 713.  60
+// channels, 73 bins, 2522 directions 1113 / 973 / 352.  One block: 60 channels 678 / 345, 32 channels 254 / 152.  With one
+// source the two forms are level (56 channels 1737 / 1775, 60: 1889 / 1782): the noise vectors stay.
 bool use_sig(ssl_ctx ctx, int M, int p, int Ns, bool gevd)
 {
+    constexpr int kEmptyRows[5] = {-1, -1, 2, 12, 7};        // at most, by tiles
     const int tiles = (M + 15) / 16;
-    if (gevd && (Ns < 2 || M <= 16 || M > 60 || 16 * tiles - M > tiles)) return false;
+    if (gevd && (Ns < 2 || M > 60 || 16 * tiles - M > kEmptyRows[tiles])) return false;
     return ctx->proj == SSL_PROJ_SIGNAL && p == 2 && ctx->svd == SSL_SVD_JACOBI && Ns >= 1 && Ns <= 3;
 }
 
