@@ -660,21 +660,37 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
              });
 }
 
+// Calls fn with the table reader of prec and kq.
+template <class KQ, class Fn>
+hipError_t with_table(ssl_prec prec, KQ kq, Fn &&fn)
+{
+    if (prec == SSL_BF16) return fn(TabBF16(), kq);
+    if (prec == SSL_FP16) return fn(TabF16(), kq);
+    return fn(TabF32(), kq);
+}
 // Calls fn with the table reader of prec and the k-steps of a class.
 template <class Fn>
 hipError_t with_variant(ssl_prec prec, int cls, Fn &&fn)
 {
-    auto table = [&](auto kq) {
-        if (prec == SSL_BF16) return fn(TabBF16(), kq);
-        if (prec == SSL_FP16) return fn(TabF16(), kq);
-        return fn(TabF32(), kq);
-    };
+    auto table = [&](auto kq) { return with_table(prec, kq, fn); };
     switch (cls) {
     case 16: return table(std::integral_constant<int, 4>());
     case 32: return table(std::integral_constant<int, 8>());
     case 48: return table(std::integral_constant<int, 12>());
     case 60: return table(std::integral_constant<int, 15>());
     default: return table(std::integral_constant<int, 16>());
+    }
+}
+
+// The same for the classes that take the GEVD form (use_sig, abi.hip).
+template <class Fn>
+hipError_t with_gevd_variant(ssl_prec prec, int cls, Fn &&fn)
+{
+    switch (cls) {
+    case 32: return with_table(prec, std::integral_constant<int, 8>(), fn);
+    case 48: return with_table(prec, std::integral_constant<int, 12>(), fn);
+    case 60: return with_table(prec, std::integral_constant<int, 15>(), fn);
+    default: return hipErrorInvalidValue;
     }
 }
 
@@ -743,7 +759,7 @@ hipError_t launch_steer_gevd(const ssl_c128 *W, const void *H, ssl_prec hprec, c
                              float *P, int per_wg, hipStream_t st)
 {
     const int nt = (steer_sig_tiles(D) + per_wg - 1) / per_wg;
-    return with_variant(hprec, steer_sig_class(M), [&](auto tab, auto kq) {
+    return with_gevd_variant(hprec, steer_sig_class(M), [&](auto tab, auto kq) {
         typedef decltype(tab) Tab;
         hipLaunchKernelGGL((steer_gevd_single<Tab, (kq + 3) / 4, kq>), dim3(sig_grid(F, nt)), dim3(kThreads),
                            0, st, reinterpret_cast<const double2 *>(W),
@@ -759,7 +775,7 @@ hipError_t launch_steer_gevd_batch(const BlockDev *blk, const int2 *items, int n
 {
     if (n_items <= 0) return hipSuccess;
     const int nt = (max_dtiles + per_wg - 1) / per_wg;
-    return with_variant(hprec, cls, [&](auto tab, auto kq) {
+    return with_gevd_variant(hprec, cls, [&](auto tab, auto kq) {
         typedef decltype(tab) Tab;
         hipLaunchKernelGGL((steer_gevd_batch<Tab, (kq + 3) / 4, kq>), dim3(sig_grid(n_items, nt)),
                            dim3(kThreads), 0, st, blk, items, n_items, nt, groups, gblocks, per_wg);
