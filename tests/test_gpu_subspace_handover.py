@@ -121,3 +121,22 @@ def test_lists_of_bins_left(S, ctx):  # noqa: F811
                 cv = to_host(c["cv"])
                 assert np.all(cv >= 0)
                 assert np.array_equal(seen.setdefault((kind, n), cv), cv)
+
+
+@pytest.mark.parametrize("kind", ["zero bins", "rank one"])
+@pytest.mark.parametrize("M", [8, 16, 33, 60])
+def test_left_bins_among_others(S, ctx, M, kind):  # noqa: F811
+    """P-bar of a block with undefined bins (zero, or without a second signal) is that of its defined bins
+    plus that of the others: what is left to the Jacobi solve changes nothing in the bins beside it."""
+    F, T, grid = 29, 40, synth.DirectionGrid(24, 2)
+    X, H = scene(F, M, T, grid, 0.7, M)
+    out = np.arange(F) % 5 == 2
+    X[out] = 0 if kind == "zero bins" else scene(F, M, T, grid, 0.0, M + 3, floor=0.0)[0][out]
+    th = sigma(X) ** 2
+    assert np.all(th[out, 1] <= 1e-12 * th[out, 0]) and np.all(th[~out, 1] > 1e-4 * th[~out, 0])
+    full = single(S, ctx, X, H, grid)
+    parts = [single(S, ctx, np.ascontiguousarray(X[m]), np.ascontiguousarray(H[m]), grid) for m in (~out, out)]
+    assert np.all(full["st"] == 0) and np.all(parts[0]["st"] == 0)
+    want = parts[0]["Pbar"].astype(np.float64) + parts[1]["Pbar"]
+    # a sum of F terms in another order: F 2^-24
+    assert np.all(np.abs(full["Pbar"] - want) <= F * 2.0 ** -24 * want)
