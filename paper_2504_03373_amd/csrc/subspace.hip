@@ -62,7 +62,7 @@ constexpr int kMaxSteps = 64;        // applications of A A^H before the Jacobi 
 constexpr int kFirstTest = 2;        // first application tested for convergence
 constexpr int kSolved = -1, kLeft = -2;                // verdicts besides a filter's degree
 constexpr int kMaxSweeps = 12;       // Jacobi sweeps over the 8 x 8 Gram matrix
-constexpr double kCouple = 1e-6;     // (S-rest coupling / gap)^2 that the first-order test copes with,
+constexpr double kCouple = 1e-7;     // (S-rest coupling / gap)^2 that the first-order test copes with,
 constexpr double kCoupleAll = 1e-9;  // and where the block is the whole space: nothing else is to converge
 constexpr int kAccel = 3;            // first step followed by a Chebyshev filter when not done
 // A filter of degree d multiplies what V's columns hold of direction 1 (2^-53) by about (4 theta_1 / theta_C)^d, where
@@ -241,9 +241,10 @@ __device__ __forceinline__ double2 conjd(double2 v) { return make_double2(v.x, -
 // rotations accumulated into Q, if the first-order Ritz vectors of the test would not do (a squared
 // coupling of more than `first` of the gap's square): until the leading Ns indices are decoupled from
 // the rest to `couple` (in order) and the rest among themselves enough for the test's bound, or to rounding (`noise`:
-// an absolute level of it for G's squared entries).  The pairs of a round are (i, i ^ m), m = 1 .. 7.
+// an absolute level of it for G's squared entries; `lost`: the share of the first diagonal entry below which one of
+// the leading Ns is not worth it).  The pairs of a round are (i, i ^ m), m = 1 .. 7.
 __device__ __forceinline__ void ritz(double2 &G, double2 &Q, int Ns, double first, double couple, double noise,
-                                     int lane)
+                                     double lost, int lane)
 {
     const int i = lane >> 3, j = lane & 7;
     for (int sw = 0; sw < kMaxSweeps; ++sw) {
@@ -256,7 +257,7 @@ __device__ __forceinline__ void ritz(double2 &G, double2 &Q, int Ns, double firs
         double ds = readlane64(G.x, 0);                // smallest of the leading diagonal
         if (Ns > 1) ds = fmin(ds, readlane64(G.x, 9));
         if (Ns > 2) ds = fmin(ds, readlane64(G.x, 18));
-        if (ds <= 1e-23 * readlane64(G.x, 0)) return;  // theta below kRange: it will be given up
+        if (ds <= lost * readlane64(G.x, 0)) return;   // theta below kRange: it will be given up
         const double below = fmax(ds - di, 0.0);
         bool bad = false;
         if (i < Ns && j >= Ns) bad = !none && !(g2 <= lim * d * d && d > 0.0);
@@ -636,7 +637,7 @@ __device__ __forceinline__ bool subspace_bin(const double2 *__restrict__ Kf, int
             double2 Q = make_double2(i == j ? 1.0 : 0.0, 0.0);
             if (step >= kFirstTest || whole)
                 ritz(G, Q, Ns, whole ? kCoupleAll : step == kFirstTest ? 1e-2 : kCouple, whole ? kCoupleAll : kCouple,
-                     step < kFirstTest ? 2e-28 : 0.0, ln);
+                     step < kFirstTest ? 2e-28 : 0.0, plain && !whole ? 1e-23 : 0.0, ln);
             const double2 a = orth_factor(G, Q, ln);
             if (step == kStart) {
                 const bool gone = whole ? G.x < kRange * readlane64(G.x, 0) : a.x == 0.0 && a.y == 0.0;
