@@ -1973,7 +1973,7 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         }
         int at = 0;
         for (size_t g = 0; g < members.size(); ++g) {
-            // by Ns: the signal-subspace projection packs its column tiles with blocks of one Ns
+            // by Ns: the signal-subspace projection packs its column tiles in this order
             std::stable_sort(members[g].begin(), members[g].end(),
                              [&](int x, int y) { return hb[x].Ns < hb[y].Ns; });
             hg[g] = make_int2(at, (int)members[g].size());

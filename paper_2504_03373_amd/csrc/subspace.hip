@@ -28,9 +28,9 @@
 // lost.  The magnitude of A does not matter: it is scaled by a power of two first, and the result has unit
 // length.
 //   One 60-channel block, two sources asked for, us with the whitening and Jacobi launches / with this (257 bins,
-// 72 directions, no noise set): one source over a floor 20 dB below 559 / 168, 40 dB below 508 / 653, no source and 50
-// frames 476 / 158, 5000 frames 1249 / 933, silence 72 / 73, one source alone 74 / 90.  Up to 16 channels long
-// averages of noise alone take longer than before (16 channels, 500 frames: 104 / 153).
+// 72 directions, no noise set): one source over a floor 20 dB below 559 / 175, 40 dB below 508 / 689, no source and 50
+// frames 476 / 154, 5000 frames 1249 / 934, silence 72 / 73, one source alone 74 / 88, R = I 187 / 241.  Up to 16
+// channels long averages of noise alone take longer than before (16 channels, 500 frames: 104 / 148).
 //
 // What bounds it: the FP64 matrix cores (64 cycles per v_mfma_f64_16x16x4f64 and SIMD: about 11.5k
 // for A, 1.9k per FP64 product, 1.3k per step for the small matrices) and, with one block per launch,
@@ -45,11 +45,12 @@
 // of a wave's rows take four MFMAs straight from the result registers.  The 8 x 8 work runs on one
 // complex element per lane, wave 1 (orthonormalisation) beside wave 0 (test).
 //   Measured, 128 60-channel blocks per launch (32896 bins): 2.5 ms, where the whitening launch (0.98 ms)
-// and the Jacobi launch (6.8 ms) stood before; one block (257 bins): 93 us, 18.7 + 505 us before.
+// and the Jacobi launch (6.8 ms) stood before; one block (257 bins): 84 to 105 us by
+// input, 18.7 + 505 us before.
 //   Up to 16 channels one wave does all of a bin, tests before it orthonormalises, and with up to 8
 // starts from the whole range of A, so that one Jacobi solve of the 8 x 8 matrix and one application decide.
-// 8 channels, 257 bins: 14.6 us; the whitening and Jacobi launches took 2.5 + 23.5 us.  24 blocks each of 8 and
-// of 16 channels with 257 and 513 bins: 0.11 and 0.135 ms (Jacobi: 0.175 and 0.25 ms, whitening 0.017).
+// 8 channels, 257 bins: 17.5 us; the whitening and Jacobi launches took 2.5 + 23.5 us.  24 blocks each of 8 and
+// of 16 channels with 257 and 513 bins: 0.126 and 0.108 ms (Jacobi: 0.175 and 0.25 ms, whitening 0.017).
 #include "signal_out.h"
 
 namespace {
