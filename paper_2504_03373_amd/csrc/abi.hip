@@ -1198,15 +1198,22 @@ int whiten_run_length(const std::vector<int> &n, const std::vector<int> &F, int 
     return best_c;
 }
 
+// After a batch that failed between its launches: its last one, which clears the lists of bins left, may not
+// have run, and the next batch must not append to them.  It takes new counters.
+void counters_drop(ssl_ctx ctx)
+{
+    clear_graphs(ctx);
+    dev_free(ctx, ctx->counters, ctx->n_counters * sizeof(unsigned int));
+    ctx->counters = nullptr;
+    ctx->n_counters = 0;
+}
+
 ssl_status counters_reserve(ssl_ctx ctx, size_t n)
 {
     if (ctx->n_counters >= n) return SSL_OK;
     size_t want = n < 256 ? 256 : n;
     if (want < 2 * ctx->n_counters) want = 2 * ctx->n_counters;
-    clear_graphs(ctx);
-    dev_free(ctx, ctx->counters, ctx->n_counters * sizeof(unsigned int));
-    ctx->counters = nullptr;
-    ctx->n_counters = 0;
+    counters_drop(ctx);
     void *p = nullptr;
     ssl_status s = dev_alloc(ctx, &p, want * sizeof(unsigned int), "batch counters");
     if (s != SSL_OK) return s;
@@ -2020,7 +2027,9 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
 
     if (!ctx->use_graphs || ctx->timing) {
         e = enqueue_batch(ctx, plan, db, dl, ga, dgevd, prec, st);
-        return e == hipSuccess ? SSL_OK : hip_fail(e, "batch launch");
+        if (e == hipSuccess) return SSL_OK;
+        counters_drop(ctx);
+        return hip_fail(e, "batch launch");
     }
     hipGraphExec_t exec = nullptr;
     for (auto &g : ctx->graphs)
@@ -2050,7 +2059,9 @@ ssl_status ssl_localize_batch(ssl_ctx ctx, const ssl_block_desc *descs, int nblo
         ctx->graphs.push_back({key, exec});
     }
     e = hipGraphLaunch(exec, st);
-    return e == hipSuccess ? SSL_OK : hip_fail(e, "hipGraphLaunch");
+    if (e == hipSuccess) return SSL_OK;
+    counters_drop(ctx);
+    return hip_fail(e, "hipGraphLaunch");
 }
 
 ssl_status ssl_noise_update_frames_from(ssl_ctx ctx, int n, const ssl_noise *dst,
